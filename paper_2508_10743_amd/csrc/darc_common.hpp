@@ -276,6 +276,21 @@ __device__ __forceinline__ void store_masked(const MaskedOut& m, uint32_t i, flo
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), m.r, off, 0, 0);
 }
 
+// Loads through the same range check: byte offsets of kNoAccess or more
+// return zero without a memory access.
+constexpr uint32_t kNoAccess = 0x80000000u;
+struct MaskedIn {
+  __amdgpu_buffer_rsrc_t r;
+};
+__device__ __forceinline__ MaskedIn masked_in(const float* base, uint32_t count) {
+  MaskedIn m;
+  m.r = masked_out(const_cast<float*>(base), count).r;
+  return m;
+}
+__device__ __forceinline__ float load_masked(const MaskedIn& m, uint32_t byte_offset) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(m.r, byte_offset, 0, 0));
+}
+
 // The 8 corners of one field component at a border cell (always in range).
 __device__ __forceinline__ void corners_border(const float* __restrict__ f, const Geom& g,
                                                int base, float (&c)[8]) {

@@ -130,6 +130,10 @@ __device__ __forceinline__ void flush_reach(int rmax, int* __restrict__ reach, i
   if (threadIdx.x < 6 && rmax > 0) atomicMax(reach + s * 8 + threadIdx.x, rmax);
 }
 
+// Entry of reach[s * 8 ..] that the reach-1 adjoint sets when it met a gradient
+// that is not finite (zeroed with the reaches).
+constexpr int kNonFinite = 6;
+
 // Records only (for an adjoint whose forward pass did not record them).
 template <bool FIRST>
 __global__ __launch_bounds__(ENT) void k_exp_rec(const float* __restrict__ src, TileGeom tg,
@@ -421,10 +425,11 @@ __device__ __forceinline__ void exp_bwd_tiled_body(TiledBwdLds& L, uint32_t blk,
   const int lx = threadIdx.x % BTX, ly = (threadIdx.x / BTX) % BTY, lz = threadIdx.x / (BTX * BTY);
   {
     // subjects with reach 2 or less everywhere are handled by the marching
-    // kernels: skip the rest of this subject's tiles
+    // kernels (but for one whose gradient is not finite): skip the rest of
+    // this subject's tiles
     const int* rc = reach + s * 8;
     if (!ALL && rc[0] <= 2 && rc[1] <= 2 && rc[2] <= 2 && rc[3] <= 2 && rc[4] <= 2 &&
-        rc[5] <= 2) {
+        rc[5] <= 2 && !rc[kNonFinite]) {
       bid = static_cast<uint32_t>(s + 1) * bg.ntiles - 1;
       continue;
     }
@@ -655,379 +660,331 @@ __global__ __launch_bounds__(BNT) void k_exp_bwd(const float* __restrict__ ut,
 
 // Adjoint of one squaring step, marching, for a subject whose every cell
 // offset lies in [-1, 0] (reach 1 in every direction: all |u_t| < 1, the
-// case of the early sweeps and of the first squaring steps).  A source in
-// plane p then falls in cell plane p-1 or p, and cell plane c feeds exactly
-// target planes c (as corner a = 0 of its cells) and c + 1 (corner a = 1).
-// So one cell plane is live at a time: iteration z fills cell plane z and one
-// pass over it completes the targets of plane z (their a = 1 part came from
-// cell plane z - 1 in the previous iteration) and starts those of plane
-// z + 1, kept in registers.  Each slot read serves both targets, which share
-// the in-plane weight; the block's LDS (one cell plane, two overflow planes,
-// the u ring) stays near a quarter of the CU's.  Iteration z: (i) clear the
-// cell plane and target plane z+1's overflow, stage u_t of plane z+1; (ii)
-// cells of the plane-(z+1) sources; (iii) fill cell plane z with the plane-z
-// sources whose cell is in it (cells kept from the last iteration) and the
-// plane-(z+1) sources whose cell is in it (one LDS integer atomic each, two
-// zero-initialised slots per cell, further sources into the overflow
-// accumulator); (iv) the direct term g + J^T g of the plane-z targets; (v)
-// the gather over the four cells around each column.  Thread (ly, lx) stages
-// and bins its own voxel, so a voxel's cell and g stay in its registers from
-// staging to its direct term; threads below 84 also stage one voxel of the
-// one-voxel halo ring.  Blocks of subjects with a larger reach return at
-// once: the tiled kernel handles those.
-constexpr int MCX = ETX + 1, MCY = ETY + 1;  // cells per cell plane: 33 x 9
-constexpr int MCP = MCX * MCY;
-constexpr int MRING = MHP - ENT;             // halo ring positions (84)
+// case of the early sweeps and of the first squaring steps).
+//
+// With |u| <= 1 the trilinear weight of source x on target y is a product of
+// hat functions, prod_d max(0, 1 - |x_d + u_d - y_d|), and along each axis the
+// hat at target offset +1, 0, -1 is max(u, 0), 1 - |u|, max(-u, 0): one
+// instruction from the source's displacement, no cell, no bin.  A target
+// gathers from the 3 x 3 x 3 sources around it.  Marching over source planes
+// q, each target column sums over the 9 in-plane sources, w their in-plane
+// weight,
+//   S0 = sum w g,  Sa = sum w |u0| g,  Ss = sum w u0 g,
+// which give the plane's contributions to target planes q (S0 - Sa), q + 1
+// ((Sa + Ss) / 2) and q - 1 ((Sa - Ss) / 2); a target is complete once its
+// plane, the one before and the one after have been walked, and its partial
+// sums stay in registers.
+//
+// Bound by vector issue: about 290 vector instructions per voxel at 85 % of
+// the issue slots, 6 TB/s out of L2 beside it.  The 9 pairs take 12
+// instructions each; threads own two adjacent rows of a 32 x 16 column, so
+// that a source read from LDS serves up to six pairs and the staged halo is
+// 1.2x the tile.  16 x 160 x 192 x 224, one step: 1.17 ms; binning the sources
+// by cell instead (an LDS atomic and 24 bytes written per source, two slots of
+// four cells read per target, the bins cleared per plane, 32 x 8 columns: 362
+// vector instructions) took 1.40 ms.  16 x 160 x 192 x 160: 0.76 and 0.95 ms.
+//
+// Border clamping moves a source whose position leaves the volume onto its
+// face: the staged u is clamped to [-1, 1] (a voxel next to a face may point
+// outwards by any amount and still have its cell within reach 1), and to
+// zero outwards on a face.  Positions outside the volume are staged with
+// g = 0.
+//
+// A source contributes to the eight corners of its cell only, so a target
+// next to it must not see 0 * g when g is not finite.  A block that meets
+// such a g says so in its subject's record (kNonFinite), and the tiled kernel,
+// launched after this one, then computes that subject again.
+constexpr int HTY = 16;                        // rows of a column (two per thread)
+constexpr int HHX = ETX + 2, HHY = HTY + 2;    // staged plane with halo: 34 x 18
+constexpr int HHP = HHX * HHY;                 // 612 positions
+constexpr int HRING = HHP - 2 * ENT;           // halo positions (100)
+
+struct HatGeom {
+  Geom g;
+  int ntx, nty, nzc, tz;  // columns and chunks along d0
+  uint32_t total;
+};
+
+HatGeom make_hat(const TileGeom& tg, int tz) {
+  HatGeom h;
+  h.g = tg.g;
+  h.ntx = tg.ntx;
+  h.nty = (tg.g.d1 + HTY - 1) / HTY;
+  h.tz = tz;
+  h.nzc = (tg.g.d0 + tz - 1) / tz;
+  h.total = static_cast<uint32_t>(h.ntx) * h.nty * h.nzc * (tg.total / tg.ntiles);
+  return h;
+}
+
+struct HatLds {
+  float uring[3][3][HHP];  // u_t of planes q-2, q-1, q (slot p % 3)
+  float4 src4[HHP];        // plane q: clamped u (scaled in the first step), g0
+  float2 src2[HHP];        // g1, g2
+};
+
+// Hat function of a displacement u at target offset d (-1, 0 or 1), |u| <= 1.
+__device__ __forceinline__ float hat(float u, int d) {
+  return d == 0 ? 1.0f - fabsf(u) : __builtin_amdgcn_fmed3f(d > 0 ? u : -u, 0.0f, 1.0f);
+}
+
+// Sums over the in-plane sources of plane q for the two targets whose first
+// source is staged at `at` (two rows of one column).
+__device__ __forceinline__ void hat_pairs(const HatLds& L, int at, float (&s0)[2][3],
+                                          float (&sa)[2][3], float (&ss)[2][3]) {
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s0[r][c] = sa[r][c] = ss[r][c] = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const float4 p = L.src4[at + j * HHX + i];
+      const float2 q = L.src2[at + j * HHX + i];
+      // the source lies i - 1 columns and j - 1 - r rows from the target
+      const float hx = hat(p.z, 1 - i);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int dy = r + 1 - j;
+        if (dy < -1 || dy > 1) continue;
+        const float w = hx * hat(p.y, dy), wz = w * p.x;
+        s0[r][0] = fmaf(w, p.w, s0[r][0]);
+        s0[r][1] = fmaf(w, q.x, s0[r][1]);
+        s0[r][2] = fmaf(w, q.y, s0[r][2]);
+        sa[r][0] = fmaf(fabsf(wz), p.w, sa[r][0]);
+        sa[r][1] = fmaf(fabsf(wz), q.x, sa[r][1]);
+        sa[r][2] = fmaf(fabsf(wz), q.y, sa[r][2]);
+        ss[r][0] = fmaf(wz, p.w, ss[r][0]);
+        ss[r][1] = fmaf(wz, q.x, ss[r][1]);
+        ss[r][2] = fmaf(wz, q.y, ss[r][2]);
+      }
+    }
+  }
+}
+
+// Range of the displacement along one axis that stays inside the volume, as
+// two bytes (-lo, hi), each 0 or 1: a position within reach 1 is clamped to
+// [x + lo, x + hi].
+__device__ __forceinline__ uint32_t hat_range(int x, int D) {
+  return static_cast<uint32_t>(x > 0) | (static_cast<uint32_t>(x < D - 1) << 8);
+}
+__device__ __forceinline__ float hat_clamp(float u, uint32_t range) {
+  return __builtin_amdgcn_fmed3f(u, -static_cast<float>(range & 255u),
+                                 static_cast<float>((range >> 8) & 255u));
+}
 
 template <bool FIRST>
-__global__ __launch_bounds__(ENT, 4) void k_exp_bwd_march(const float* __restrict__ ut,
-                                                          const float* __restrict__ gin,
-                                                          float* __restrict__ gout, MarchGeom m,
-                                                          float scale, float oscale,
-                                                          const int* __restrict__ reach) {
-  __shared__ float uring[3][3][MHP];  // u_t of planes z-1, z, z+1 (slot p % 3)
-  __shared__ int bcnt[MCP];           // the live cell plane
-  __shared__ float4 bd4[KSLOT][MCP];  // t0, t1, t2, g0 per binned source (0 if empty)
-  __shared__ float2 bd2[KSLOT][MCP];  // g1, g2
-  __shared__ float ovf[2][3][ENT];    // overflow into target planes, by parity
-  const Geom& g = m.rec.g;
-  const MarchId id = march_id(m);
+__global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict__ ut,
+                                                        const float* __restrict__ gin,
+                                                        float* __restrict__ gout, HatGeom m,
+                                                        float scale, float oscale,
+                                                        int* __restrict__ reach) {
+  __shared__ HatLds L;
+  const Geom& g = m.g;
+  uint32_t b = xcd_remap(blockIdx.x, m.total);
+  const int ox = static_cast<int>(b % m.ntx) * ETX;
+  b /= m.ntx;
+  const int oy = static_cast<int>(b % m.nty) * HTY;
+  b /= m.nty;
+  const int z0 = static_cast<int>(b % m.nzc) * m.tz, z1 = min(z0 + m.tz, g.d0);
+  const int s = static_cast<int>(b / m.nzc);
   {
-    const int* rc = reach + id.s * 8;
+    const int* rc = reach + s * 8;
     if (rc[0] > 1 || rc[1] > 1 || rc[2] > 1 || rc[3] > 1 || rc[4] > 1 || rc[5] > 1) return;
   }
-  const size_t off = static_cast<size_t>(id.s) * 3 * g.V;
-  const float* f = ut + off;
-  const float* gi = gin + off;
-  float* go = gout + off;
-  const int lx = threadIdx.x % ETX, ly = threadIdx.x / ETX;
-  const float js = FIRST ? scale : 1.0f;
+  const size_t off = static_cast<size_t>(s) * 3 * g.V;
+  MaskedOut out[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    out[c] = masked_out(gout + off + static_cast<size_t>(c) * g.V, static_cast<uint32_t>(g.V));
+  const int tid = threadIdx.x, lx = tid % ETX, ry = tid / ETX;
+  const float js = FIRST ? 2.0f * scale : 2.0f;  // sums are kept doubled (see the update below)
+  const float os = 0.5f * oscale;
 
-  // staged positions: j = 0 the thread's own voxel, j = 1 a halo-ring voxel
-  int pe[2], py[2], px[2], poff[2];
-  bool puse[2], pin[2];
-  pe[0] = (ly + 1) * MHX + lx + 1;
-  py[0] = id.oy + ly;
-  px[0] = id.ox + lx;
-  puse[0] = true;
+  // Staged positions of this thread: its two targets (rows 2 ry and 2 ry + 1)
+  // and, for the first HRING threads, one of the halo ring.  Positions outside
+  // the volume (and threads without a ring position) load past the range
+  // check and get zeros.
+  const int at0 = 2 * ry * HHX + lx;  // staged position of the first target's first source
+  const int x2 = ox + lx, y1 = oy + 2 * ry;
+  int pr;                 // the ring position
+  uint32_t poff[3];       // byte offsets within a plane
+  uint32_t prange[3];     // clamping ranges along d2 and d1
   {
-    const int r = threadIdx.x;
     int hy, hx;
-    if (r < MHX) {
-      hy = 0;
-      hx = r;
-    } else if (r < 2 * MHX) {
-      hy = MHY - 1;
-      hx = r - MHX;
-    } else if (r < 2 * MHX + ETY) {
-      hy = 1 + r - 2 * MHX;
-      hx = 0;
+    if (tid < 2 * HHX) {
+      hy = tid < HHX ? 0 : HHY - 1;
+      hx = tid < HHX ? tid : tid - HHX;
     } else {
-      hy = 1 + min(r - 2 * MHX - ETY, ETY - 1);
-      hx = MHX - 1;
+      const int q = min(tid - 2 * HHX, 2 * HTY - 1);
+      hy = 1 + (q >> 1);
+      hx = (q & 1) * (HHX - 1);
     }
-    puse[1] = r < MRING;
-    pe[1] = hy * MHX + hx;
-    py[1] = id.oy - 1 + hy;
-    px[1] = id.ox - 1 + hx;
+    pr = hy * HHX + hx;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int y = j < 2 ? y1 + j : oy - 1 + hy, x = j < 2 ? x2 : ox - 1 + hx;
+      const bool in = y >= 0 && y < g.d1 && x >= 0 && x < g.d2 && (j < 2 || tid < HRING);
+      poff[j] = in ? static_cast<uint32_t>(y * g.d2 + x) << 2 : kNoAccess;
+      prange[j] = hat_range(x, g.d2) | (hat_range(y, g.d1) << 16);
+    }
   }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    pin[j] = py[j] >= 0 && py[j] < g.d1 && px[j] >= 0 && px[j] < g.d2;
-    poff[j] = min(max(py[j], 0), g.d1 - 1) * g.d2 + min(max(px[j], 0), g.d2 - 1);
-  }
-  // lanes without a halo voxel load their own voxel again (a cache line the
-  // wave reads anyway) rather than fetching rows of other tiles
-  if (!puse[1]) poff[1] = poff[0];
+  const bool ring = tid < HRING;
+  // the tile or its halo touches the two outer layers of the volume in d1 or d2
+  const bool face = oy == 0 || ox == 0 || oy + HTY >= g.d1 - 2 || ox + ETX >= g.d2 - 2;
 
-  // component base pointers (uniform across the block)
-  const float* fc[3] = {f, f + g.V, f + 2 * static_cast<size_t>(g.V)};
-  const float* gc[3] = {gi, gi + g.V, gi + 2 * static_cast<size_t>(g.V)};
-  // Planes in flight: two register buffers, loaded two planes ahead of use.
-  // Every lane loads (lanes without a halo voxel from a clamped, valid
-  // position) and planes past the chunk are loaded clamped too: a
-  // conditional load would make the compiler merge register values right
-  // after it and so wait for it at once.
-  float pu[2][3], pg[2][3], pu2[2][3], pg2[2][3];
-  auto load_plane = [&](int z, float (&lu)[2][3], float (&lg)[2][3]) {
-    const int zc = min(max(z, 0), g.d0 - 1);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t lin = static_cast<uint32_t>(zc * g.plane + poff[j]);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        lu[j][c] = ld_at(fc[c], lin);
-        lg[j][c] = ld_at(gc[c], lin);
-      }
-    }
-  };
-  auto store_u = [&](int z, const float (&su_)[2][3]) {
-    const int su = (z + 3) % 3;
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      if (puse[j]) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) uring[su][c][pe[j]] = su_[j][c];
-      }
-  };
-  auto clear_cells = [&]() {
-    const float4 z4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    const float2 z2 = make_float2(0.0f, 0.0f);
-    // threads in reverse order: the cells past ENT fall to the last wave,
-    // which stages no halo voxels
-    for (int i = ENT - 1 - static_cast<int>(threadIdx.x); i < MCP; i += ENT) {
-      bcnt[i] = 0;
-#pragma unroll
-      for (int k = 0; k < KSLOT; ++k) {
-        bd4[k][i] = z4;
-        bd2[k][i] = z2;
-      }
-    }
-  };
-  auto clear_ovf = [&](int tplane) {
-    float* o = &ovf[tplane & 1][0][0];
-    for (int i = threadIdx.x; i < 3 * ENT; i += ENT) o[i] = 0.0f;
-  };
-  // cells of the staged sources of plane p (ok = a source inside the volume)
-  auto cells_of = [&](int p, const float (&vu)[2][3], BorderCell (&bc)[2], bool (&ok)[2]) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      ok[j] = puse[j] && pin[j] && p >= 0 && p < g.d0;
-      bc[j] = BorderCell{};
-      // lanes without a halo voxel (all of waves 2 and 3) skip the halo cell
-      if (puse[j]) {
-        float u0 = vu[j][0], u1 = vu[j][1], u2 = vu[j][2];
-        if (FIRST) {
-          u0 *= scale;
-          u1 *= scale;
-          u2 *= scale;
-        }
-        bc[j] = border_cell(g, min(max(p, 0), g.d0 - 1), py[j], px[j], u0, u1, u2);
-      }
-    }
-  };
-  // Bin one source into the live cell plane (its plane bc.i0 is the one
-  // being filled).  The cell of a tile voxel (halo = false) always lies in the
-  // tile's cell region (offsets in [-1, 0], and border clamping keeps a cell
-  // inside the volume); a halo voxel's cell may not.
-  auto bin_one = [&](const BorderCell& bc, float g0, float g1, float g2, bool halo) {
-    const int c1 = bc.i1 - id.oy + 1, c2 = bc.i2 - id.ox + 1;
-    if (halo && (c1 < 0 || c1 >= MCY || c2 < 0 || c2 >= MCX)) return;
-    const int ci = c1 * MCX + c2;
-    const int slot = atomicAdd(&bcnt[ci], 1);
-    if (slot < KSLOT) {
-      bd4[slot][ci] = make_float4(bc.t0, bc.t1, bc.t2, g0);
-      bd2[slot][ci] = make_float2(g1, g2);
-    } else {
-      const float w0[2] = {1.0f - bc.t0, bc.t0};
-      const float w1[2] = {1.0f - bc.t1, bc.t1};
-      const float w2[2] = {1.0f - bc.t2, bc.t2};
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int tz = bc.i0 + a;  // target plane
-        if (tz < id.z0 || tz >= id.z1) continue;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-#pragma unroll
-          for (int ee = 0; ee < 2; ++ee) {
-            const int ty = c1 + b - 1, tx = c2 + ee - 1;
-            if (ty >= 0 && ty < ETY && tx >= 0 && tx < ETX) {
-              const float w = w0[a] * w1[b] * w2[ee];
-              float* ov = &ovf[tz & 1][0][0] + ty * ETX + tx;
-              atomicAdd(ov, w * g0);
-              atomicAdd(ov + ENT, w * g1);
-              atomicAdd(ov + 2 * ENT, w * g2);
-            }
-          }
-        }
-      }
-    }
-  };
-  // One pass over the live cell plane: for each of the four cells around the
-  // thread's column and each slot, w12 = the in-plane weight of the corner
-  // (b, e); the target of the cell's lower plane (a = 0) takes w12 (1 - t0),
-  // the one of its upper plane (a = 1) w12 t0.  Empty slots hold zeros.
-  auto gather = [&](float (&lo)[3], float (&up)[3], bool upper) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int ci = (ly + 1 - b) * MCX + (lx + 1 - e);
-#pragma unroll
-        for (int j = 0; j < KSLOT; ++j) {
-          const float4 p = bd4[j][ci];
-          const float2 q = bd2[j][ci];
-          const float w1 = b ? p.y : 1.0f - p.y;
-          const float w12 = e ? w1 * p.z : fmaf(-w1, p.z, w1);
-          const float wl = fmaf(-w12, p.x, w12);
-          lo[0] += wl * p.w;
-          lo[1] += wl * q.x;
-          lo[2] += wl * q.y;
-          if (upper) {
-            const float wu = w12 * p.x;
-            up[0] += wu * p.w;
-            up[1] += wu * q.x;
-            up[2] += wu * q.y;
-          }
-        }
-      }
-    }
-  };
-
-  const bool colv = pin[0];
-  BorderCell cb[2], nb[2];  // cells of the plane-z and plane-(z+1) sources
-  bool cok[2], nok[2];
-  float cg[2][3], qu[2][3], qg[2][3];
-  // targets of the next plane, partly gathered (their a = 1 part)
-  float accA[3] = {0.0f, 0.0f, 0.0f}, accB[3] = {0.0f, 0.0f, 0.0f};
-
-  // prologue: cell plane z0-1 from the sources of planes z0-1 and z0, and
-  // its a = 1 part of the plane-z0 targets; planes z0+1 and z0+2 in flight
-  clear_cells();
-  clear_ovf(id.z0);
-  load_plane(id.z0 - 1, pu, pg);
-  store_u(id.z0 - 1, pu);
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
+  float pu[3][3], pg[3][3];
+  auto load_plane = [&](int z) {
+    // a plane outside the volume: nothing is in range
+    const uint32_t zo = static_cast<uint32_t>(min(max(z, 0), g.d0 - 1) * g.plane) << 2;
+    const uint32_t count = z >= 0 && z < g.d0 ? static_cast<uint32_t>(g.V) : 0u;
+    MaskedIn fu[3], fg[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      qu[j][c] = pu[j][c];
-      qg[j][c] = pg[j][c];
+      const size_t oc = off + static_cast<size_t>(c) * g.V;
+      fu[c] = masked_in(ut + oc, count);
+      fg[c] = masked_in(gin + oc, count);
     }
-  load_plane(id.z0, pu, pg);
-  store_u(id.z0, pu);
-  __syncthreads();
-  cells_of(id.z0 - 1, qu, nb, nok);
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
-    if (nok[j] && nb[j].i0 == id.z0 - 1) bin_one(nb[j], qg[j][0], qg[j][1], qg[j][2], j == 1);
-  cells_of(id.z0, pu, cb, cok);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (cok[j] && cb[j].i0 == id.z0 - 1) bin_one(cb[j], pg[j][0], pg[j][1], pg[j][2], j == 1);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) cg[j][c] = pg[j][c];
-  }
-  load_plane(id.z0 + 1, pu, pg);
-  load_plane(id.z0 + 2, pu2, pg2);
-  __syncthreads();
-  {
-    float none[3] = {0.0f, 0.0f, 0.0f};
-    if (colv) gather(none, accA, true);
-  }
-  __syncthreads();
-
-  // one plane; (xu, xg) holds plane z+1 on entry and takes plane z+3; acc
-  // holds the plane-z targets' a = 1 part and receives plane z+1's
-  auto step = [&](int z, float (&xu)[2][3], float (&xg)[2][3], float (&acc)[3],
-                  float (&nacc)[3]) {
-    // (i) clear the cell plane (held z-1) and target plane z+1 (held z-1);
-    //     stage u of plane z+1
-    clear_cells();
-    clear_ovf(z + 1);
-    store_u(z + 1, xu);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 3; ++j)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        qu[j][c] = xu[j][c];
-        qg[j][c] = xg[j][c];
+        pu[j][c] = load_masked(fu[c], zo + poff[j]);
+        pg[j][c] = load_masked(fg[c], zo + poff[j]);
       }
-    __syncthreads();
-    load_plane(z + 3, xu, xg);
-    // (ii) cells of the plane-(z+1) sources
-    cells_of(z + 1, qu, nb, nok);
-    // (iii) fill cell plane z
+  };
+  bool bad = false;  // a g that is not finite was staged
+  auto stage = [&](int z) {
+    const int sl = (z + 3) % 3;
+    const uint32_t rz = hat_range(z, g.d0);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (cok[j] && cb[j].i0 == z) bin_one(cb[j], cg[j][0], cg[j][1], cg[j][2], j == 1);
-      if (nok[j] && nb[j].i0 == z) bin_one(nb[j], qg[j][0], qg[j][1], qg[j][2], j == 1);
+    for (int j = 0; j < 3; ++j) {
+      if (j == 2 && !ring) continue;
+      // LDS offsets recomputed on every plane: held in registers they would
+      // cost the fourth wave per SIMD
+      int e = j < 2 ? at0 + (j + 1) * HHX + 1 : pr;
+      asm volatile("" : "+v"(e));
+      float u[3] = {pu[j][0], pu[j][1], pu[j][2]};
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        L.uring[sl][c][e] = u[c];
+        if (FIRST) u[c] *= scale;
+      }
+      if (face || z <= 1 || z >= g.d0 - 2) {
+        u[0] = hat_clamp(u[0], rz);
+        u[1] = hat_clamp(u[1], prange[j] >> 16);
+        u[2] = hat_clamp(u[2], prange[j]);
+      }
+      bad |= !__builtin_isfinite(pg[j][0] + pg[j][1] + pg[j][2]);
+      L.src4[e] = make_float4(u[0], u[1], u[2], pg[j][0]);
+      L.src2[e] = make_float2(pg[j][1], pg[j][2]);
     }
-    // (iv) direct term of the plane-z targets
-    float r[3] = {acc[0], acc[1], acc[2]};
-    const int szm = (z + 2) % 3, szc = z % 3, szp = (z + 1) % 3;  // slots of z-1, z, z+1
-    if (colv) {
-      const BorderCell& bc = cb[0];
-      const int c0 = bc.i0 - z + 1, c1 = bc.i1 - id.oy + 1, c2 = bc.i2 - id.ox + 1;
-      const bool in_ring =
-          c0 >= 0 && c0 <= 1 && c1 >= 0 && c1 + 1 < MHY && c2 >= 0 && c2 + 1 < MHX;
-      // J^T g = grad of the trilinear interpolant of g . u at the sample.
-      // Corners come from the staged ring; a cell outside it (not reached
-      // while every offset lies in [-1, 0]) reads them from memory.  The
-      // memory path combines three derivative evaluations instead of forming
-      // g . u at the corners first: its arithmetic then cannot be merged with
-      // the ring path's after the branch, which would make the ring path
-      // wait for memory loads (and with them for the planes in flight).
-      Tri t;
-      if (in_ring) {
-        // ring slots of planes i0 and i0 + 1, i0 in {z - 1, z}: uniform choices
-        const int sa = c0 ? szc : szm, sb = c0 ? szp : szc;
-        const int pb = c1 * MHX + c2;
+  };
+
+  load_plane(z0 - 1);
+  // as many (discarded) stores after the first loads as every step issues, so
+  // that the loop's first wait counts the same on both ways in
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) store_masked(out[c], 0u, 0.0f, false);
+  // twice the partial sums of the targets of planes q - 1 and q
+  float accA[2][3] = {}, accB[2][3] = {};
+  float og[2][3] = {};  // g of the targets of plane q - 1
+  for (int q = z0 - 1; q <= z1; ++q) {
+    stage(q);
+    load_plane(q + 1);
+    __syncthreads();
+    const int p = q - 1;  // the target plane finished by this step
+    int at = at0;
+    asm volatile("" : "+v"(at));
+    if (p >= z0) {
+      // ring slots (as offsets) of planes p-1, p, p+1
+      constexpr int kSlot = 3 * HHP;
+      const int slm = (p + 2) % 3 * kSlot, slc = p % 3 * kSlot, slp = (p + 1) % 3 * kSlot;
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        // direct term: J^T g = gradient of the interpolant of g . u at the
+        // sample, corners from the ring
+        const int own = at + (r + 1) * HHX + 1;
+        float u[3];
+        bool lo[3], kl[3] = {false, false, false};  // cell below x; clamped
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          u[c] = (&L.uring[0][0][0])[slc + c * HHP + own];
+          if (FIRST) u[c] *= scale;
+          lo[c] = u[c] < 0.0f;
+        }
+        if (face || p <= 1 || p >= g.d0 - 2) {
+          // clamped positions, the last cell at the far faces, no derivative
+          // along a clamped axis
+          const uint32_t rg[3] = {hat_range(p, g.d0), prange[r] >> 16, prange[r]};
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const float w = hat_clamp(u[c], rg[c]);
+            kl[c] = w != u[c];
+            u[c] = w;
+            lo[c] = w < 1.0f - static_cast<float>((rg[c] >> 8) & 255u);
+          }
+        }
+        const float f0 = u[0] + (lo[0] ? 1.0f : 0.0f), f1 = u[1] + (lo[1] ? 1.0f : 0.0f),
+                    f2 = u[2] + (lo[2] ? 1.0f : 0.0f);
+        // one component's corners: rows of planes i0 and i0 + 1
+        const int pb = own + (lo[1] ? -HHX : 0) + (lo[2] ? -1 : 0);
+        const float* ra = &L.uring[0][0][0] + (pb + (lo[0] ? slm : slc));
+        const float* rb = &L.uring[0][0][0] + (pb + (lo[0] ? slc : slp));
         float h[8];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const float cv[8] = {uring[sa][c][pb],       uring[sa][c][pb + 1],
-                               uring[sa][c][pb + MHX], uring[sa][c][pb + MHX + 1],
-                               uring[sb][c][pb],       uring[sb][c][pb + 1],
-                               uring[sb][c][pb + MHX], uring[sb][c][pb + MHX + 1]};
+          const float cv[8] = {ra[c * HHP],       ra[c * HHP + 1],
+                               ra[c * HHP + HHX], ra[c * HHP + HHX + 1],
+                               rb[c * HHP],       rb[c * HHP + 1],
+                               rb[c * HHP + HHX], rb[c * HHP + HHX + 1]};
 #pragma unroll
-          for (int k = 0; k < 8; ++k) h[k] = c == 0 ? cg[0][0] * cv[k] : h[k] + cg[0][c] * cv[k];
+          for (int k = 0; k < 8; ++k) h[k] = c == 0 ? og[r][0] * cv[k] : h[k] + og[r][c] * cv[k];
         }
-        t = tri_eval(h, bc.t0, bc.t1, bc.t2);
-      } else {
-        t.v = 0.0f;
-        t.d0 = t.d1 = t.d2 = 0.0f;
+        const Tri t = tri_eval(h, f0, f1, f2);
+        const float d[3] = {kl[0] ? 0.0f : t.d0, kl[1] ? 0.0f : t.d1, kl[2] ? 0.0f : t.d2};
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          float cv[8];
-          corners_border(fc[c], g, bc.base, cv);
-          const Tri tc = tri_eval(cv, bc.t0, bc.t1, bc.t2);
-          t.d0 += tc.d0 * cg[0][c];
-          t.d1 += tc.d1 * cg[0][c];
-          t.d2 += tc.d2 * cg[0][c];
-        }
+        for (int c = 0; c < 3; ++c)
+          accA[r][c] = fmaf(js, d[c], fmaf(2.0f, og[r][c], accA[r][c]));
       }
-      r[0] += cg[0][0] + (bc.k0 ? 0.0f : t.d0 * js);
-      r[1] += cg[0][1] + (bc.k1 ? 0.0f : t.d1 * js);
-      r[2] += cg[0][2] + (bc.k2 ? 0.0f : t.d2 * js);
+    }
+    float s0[2][3], sa[2][3], ss[2][3];
+    hat_pairs(L, at, s0, sa, ss);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int own = at + (r + 1) * HHX + 1;
+      const float2 b2 = L.src2[own];
+      og[r][0] = L.src4[own].w;
+      og[r][1] = b2.x;
+      og[r][2] = b2.y;
+    }
+    // plane q's parts, doubled: sa - ss of targets q - 1 (now complete),
+    // 2 (s0 - sa) of targets q, sa + ss of targets q + 1.  Range-checked
+    // stores on every plane: a store under a branch would make the next
+    // staging wait for it together with the plane in flight.
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const uint32_t lin = static_cast<uint32_t>(p * g.plane + (y1 + r) * g.d2 + x2);
+      const bool on = p >= z0 && x2 < g.d2 && y1 + r < g.d1;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        store_masked(out[c], lin, (accA[r][c] + (sa[r][c] - ss[r][c])) * os, on);
+        accA[r][c] = fmaf(2.0f, s0[r][c] - sa[r][c], accB[r][c]);
+        accB[r][c] = sa[r][c] + ss[r][c];
+      }
     }
     __syncthreads();
-    // (v) gather: finish the plane-z targets, start the plane-(z+1) ones
-#pragma unroll
-    for (int c = 0; c < 3; ++c) nacc[c] = 0.0f;
-    if (colv) {
-      gather(r, nacc, z + 1 < id.z1);
-      const float* ov = &ovf[z & 1][0][0];
-      r[0] += ov[threadIdx.x];
-      r[1] += ov[ENT + threadIdx.x];
-      r[2] += ov[2 * ENT + threadIdx.x];
-      const uint32_t lin = static_cast<uint32_t>(z * g.plane + py[0] * g.d2 + px[0]);
-      st_at(go, lin, r[0] * oscale);
-      st_at(go + g.V, lin, r[1] * oscale);
-      st_at(go + 2 * static_cast<size_t>(g.V), lin, r[2] * oscale);
-    }
-    // (vi) the plane-(z+1) sources become the next iteration's plane-z sources
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      cb[j] = nb[j];
-      cok[j] = nok[j];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) cg[j][c] = qg[j][c];
-    }
-    __syncthreads();
-  };
-  // unrolled by two so that each prefetch buffer and partial keeps its registers
-  for (int z = id.z0; z < id.z1; z += 2) {
-    step(z, pu, pg, accA, accB);
-    if (z + 1 < id.z1) step(z + 1, pu2, pg2, accB, accA);
   }
+  if (bad) reach[s * 8 + kNonFinite] = 1;
 }
 
 // Adjoint of one squaring step, marching, for a subject whose cell offsets
 // lie in [-2, 1] on every axis and reach beyond [-1, 0] somewhere (reach 2:
 // roughly 1 <= max |u_t| < 2, the later squaring steps of moderate
-// deformations).  The reach-1 kernel's scheme with wider windows: a source
-// of plane p falls in cell planes p-2 .. p+1, so cell plane z is filled from
+// deformations).  Sources are binned by cell, one cell plane live at a time: a
+// source of plane p falls in cell planes p-2 .. p+1, so cell plane z is filled from
 // the sources of planes z-1 .. z+2, whose cells are computed once, when their
 // plane is staged, and kept in registers for four iterations; sources up to
 // two voxels outside the column can land in its cell region (a two-voxel halo
@@ -1039,6 +996,8 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_march(const float* __restric
 // targets; (iv) the gather, finishing plane z and starting plane z+1.
 // Blocks of subjects with reach 1 everywhere (the reach-1 kernel's) or
 // beyond 2 (the tiled kernel's) return at once.
+constexpr int MCX = ETX + 1, MCY = ETY + 1;  // cells per cell plane: 33 x 9
+constexpr int MCP = MCX * MCY;
 constexpr int H2X = ETX + 4, H2Y = ETY + 4;  // staged plane with a two-voxel halo: 36 x 12
 constexpr int H2P = H2X * H2Y;               // 432 positions
 constexpr int H2RING = H2P - ENT;            // 176 halo positions
@@ -1855,7 +1814,7 @@ void launch_rec(const float* ut, bool first, const TileGeom& tg, float scale, in
 }
 
 void launch_bwd_step(const float* ut, const float* gin, float* gout, bool first, const MarchGeom& m,
-                     const BwdGeom& bg, float scale, const int* bx, const int* rc, bool planes,
+                     const BwdGeom& bg, float scale, const int* bx, int* rc, bool planes,
                      hipStream_t st) {
   prof_begin(st, KC_EXP_BWD);
   if (planes) {
@@ -1869,17 +1828,18 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, bool first,
     prof_end(st, KC_EXP_BWD);
     return;
   }
+  const HatGeom hg = make_hat(m.rec, m.tz);
   // each subject is handled by exactly one of the three kernels (decided on
   // the device from its reach: 1, 2, beyond); the others' blocks return at once
   if (first) {
-    hipLaunchKernelGGL((k_exp_bwd_march<true>), dim3(m.total), dim3(ENT), 0, st, ut, gin, gout, m,
+    hipLaunchKernelGGL((k_exp_bwd_hat<true>), dim3(hg.total), dim3(ENT), 0, st, ut, gin, gout, hg,
                        scale, scale, rc);
     hipLaunchKernelGGL((k_exp_bwd_march2<true>), dim3(march2_grid(m)), dim3(ENT), 0, st, ut, gin,
                        gout, m, scale, scale, rc);
     hipLaunchKernelGGL((k_exp_bwd<true, false>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
                        gout, bg, scale, scale, bx, rc);
   } else {
-    hipLaunchKernelGGL((k_exp_bwd_march<false>), dim3(m.total), dim3(ENT), 0, st, ut, gin, gout, m,
+    hipLaunchKernelGGL((k_exp_bwd_hat<false>), dim3(hg.total), dim3(ENT), 0, st, ut, gin, gout, hg,
                        1.0f, 1.0f, rc);
     hipLaunchKernelGGL((k_exp_bwd_march2<false>), dim3(march2_grid(m)), dim3(ENT), 0, st, ut, gin,
                        gout, m, 1.0f, 1.0f, rc);
