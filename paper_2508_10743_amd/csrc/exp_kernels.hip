@@ -397,25 +397,17 @@ struct TiledBwdLds {
   int ubox[6];  // union of the candidate source sub-boxes
 };
 
-// Blocks blk of nblk walk the adjoint tiles; ALL: every subject, otherwise
-// only those with a reach beyond 1 (the marching kernel takes the others).
-template <bool FIRST, bool ALL>
-__device__ __forceinline__ void exp_bwd_tiled_body(TiledBwdLds& L, uint32_t blk, uint32_t nblk,
-                                                   const float* __restrict__ ut,
-                                                   const float* __restrict__ gin,
-                                                   float* __restrict__ gout, const BwdGeom& bg,
-                                                   float scale, float oscale,
-                                                   const int* __restrict__ boxes,
-                                                   const int* __restrict__ reach) {
+// One tile of subject s.
+template <bool FIRST>
+__device__ __forceinline__ void exp_bwd_tile(TiledBwdLds& L, int s, int tile,
+                                             const float* __restrict__ ut,
+                                             const float* __restrict__ gin,
+                                             float* __restrict__ gout, const BwdGeom& bg,
+                                             float scale, float oscale,
+                                             const int* __restrict__ boxes,
+                                             const int* __restrict__ reach) {
   const TileGeom& tg = bg.src;
   const Geom& g = tg.g;
-  // persistent: each block walks a contiguous run of tiles (runs of
-  // neighbouring blocks sit on the same XCD)
-  const uint32_t run = (bg.total + nblk - 1) / nblk;
-  const uint32_t first = xcd_remap(blk, nblk) * run;
-  for (uint32_t bid = first; bid < min(first + run, bg.total); ++bid) {
-  const int s = static_cast<int>(bid / bg.ntiles);
-  const int tile = static_cast<int>(bid - static_cast<uint32_t>(s) * bg.ntiles);
   const int ox = (tile % bg.ntx) * BTX;
   const int oy = ((tile / bg.ntx) % bg.nty) * BTY;
   const int oz = (tile / (bg.ntx * bg.nty)) * BTZ;
@@ -423,17 +415,6 @@ __device__ __forceinline__ void exp_bwd_tiled_body(TiledBwdLds& L, uint32_t blk,
   const int L1 = min(oy + BTY, g.d1) - 1;
   const int L2 = min(ox + BTX, g.d2) - 1;
   const int lx = threadIdx.x % BTX, ly = (threadIdx.x / BTX) % BTY, lz = threadIdx.x / (BTX * BTY);
-  {
-    // subjects with reach 2 or less everywhere are handled by the marching
-    // kernels (but for one whose gradient is not finite): skip the rest of
-    // this subject's tiles
-    const int* rc = reach + s * 8;
-    if (!ALL && rc[0] <= 2 && rc[1] <= 2 && rc[2] <= 2 && rc[3] <= 2 && rc[4] <= 2 &&
-        rc[5] <= 2 && !rc[kNonFinite]) {
-      bid = static_cast<uint32_t>(s + 1) * bg.ntiles - 1;
-      continue;
-    }
-  }
   const size_t off = static_cast<size_t>(s) * 3 * g.V;
   const float* f = ut + off;
   const float* gi = gin + off;
@@ -480,10 +461,13 @@ __device__ __forceinline__ void exp_bwd_tiled_body(TiledBwdLds& L, uint32_t blk,
   // 2. bin the source voxels whose cell base lies in [O - 1, L].  A source x
   //    of forward tile s has its cell base in x + [min, max] (the recorded
   //    offsets), so only x_d in [O_d - 1 - max_d, L_d - min_d] can qualify;
-  //    candidate forward tiles come from the subject-wide reach.  The union
+  //    candidate forward tiles come from the subject-wide reach (recorded
+  //    only from 2 on by the plane-parallel forward).  The union
   //    box of those sub-boxes is swept as one flattened range, four sources
   //    per thread at a time with all their loads issued before any is used.
-  const int* rc = reach + s * 8;
+  int rc[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) rc[k] = max(reach[s * 8 + k], 1);
   const int lo0 = max(0, oz - rc[3]) / ETZ, hi0 = min(tg.ntz - 1, (L0 + rc[0]) / ETZ);
   const int lo1 = max(0, oy - rc[4]) / ETY, hi1 = min(tg.nty - 1, (L1 + rc[1]) / ETY);
   const int lo2 = max(0, ox - rc[5]) / ETX, hi2 = min(tg.ntx - 1, (L2 + rc[2]) / ETX);
@@ -643,10 +627,12 @@ __device__ __forceinline__ void exp_bwd_tiled_body(TiledBwdLds& L, uint32_t blk,
     go[2 * g.V + lin] = r2 * oscale;
   }
   __syncthreads();  // the next tile reuses the LDS bins
-  }
 }
 
-template <bool FIRST, bool ALL>
+// Subjects with a cell offset beyond [-2, 1], and those whose gradient is not
+// finite; the marching kernels take the others.  Persistent: each block walks
+// a contiguous run of tiles (runs of neighbouring blocks sit on the same XCD).
+template <bool FIRST>
 __global__ __launch_bounds__(BNT) void k_exp_bwd(const float* __restrict__ ut,
                                                  const float* __restrict__ gin,
                                                  float* __restrict__ gout, BwdGeom bg,
@@ -654,8 +640,19 @@ __global__ __launch_bounds__(BNT) void k_exp_bwd(const float* __restrict__ ut,
                                                  const int* __restrict__ boxes,
                                                  const int* __restrict__ reach) {
   __shared__ TiledBwdLds L;
-  exp_bwd_tiled_body<FIRST, ALL>(L, blockIdx.x, gridDim.x, ut, gin, gout, bg, scale, oscale,
-                                 boxes, reach);
+  const uint32_t run = (bg.total + gridDim.x - 1) / gridDim.x;
+  const uint32_t first = xcd_remap(blockIdx.x, gridDim.x) * run;
+  for (uint32_t bid = first; bid < min(first + run, bg.total); ++bid) {
+    const int s = static_cast<int>(bid / bg.ntiles);
+    const int* rc = reach + s * 8;
+    if (rc[0] <= 2 && rc[1] <= 2 && rc[2] <= 2 && rc[3] <= 2 && rc[4] <= 2 && rc[5] <= 2 &&
+        !rc[kNonFinite]) {
+      bid = static_cast<uint32_t>(s + 1) * bg.ntiles - 1;  // the rest of this subject's tiles
+      continue;
+    }
+    exp_bwd_tile<FIRST>(L, s, static_cast<int>(bid - static_cast<uint32_t>(s) * bg.ntiles), ut,
+                        gin, gout, bg, scale, oscale, boxes, reach);
+  }
 }
 
 // Adjoint of one squaring step, marching, for a subject whose every cell
@@ -978,6 +975,194 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
     __syncthreads();
   }
   if (bad) reach[s * 8 + kNonFinite] = 1;
+}
+
+// The same gather without marching, for volumes too small to fill the chip with
+// columns: a block owns 32 x 8 x 2 targets (two per thread, along d0), stages
+// the 34 x 10 x 4 sources around them at once and every thread sums over its
+// 3 x 3 x 4.  Bound by latency (one load round, one barrier, about 550 vector
+// instructions per wave at a wave or two per SIMD): tiles of 512 targets give
+// 4 x 32^3 one block per CU.  A subject with a larger reach takes the binning
+// tile in the same launch (an idle launch would cost a third of this kernel).
+// 4 x 32^3, one step: 6.4 us; the binning tile for every subject took 12.7 us.
+constexpr int NTY = 8, NTZ = 2;                       // rows and planes of a tile
+constexpr int NHY = NTY + 2, NHZ = NTZ + 2;
+constexpr int NHP = HHX * NHY * NHZ;                  // 1360 staged positions
+constexpr int NNJ = (NHP + ENT - 1) / ENT;            // per thread (6)
+
+struct NearLds {
+  float uraw[3][NHP];  // u_t
+  float4 src4[NHP];    // clamped u (scaled in the first step), g0
+  float2 src2[NHP];    // g1, g2
+  int nonfinite;
+};
+
+struct NearGeom {
+  BwdGeom bg;                // the binning tiles
+  int nty, ntz;              // near tiles (as many along d2 as bg)
+  int items;                 // blocks per subject: the larger of the two counts
+};
+
+NearGeom make_near(const BwdGeom& bg) {
+  NearGeom ng;
+  ng.bg = bg;
+  ng.nty = (bg.src.g.d1 + NTY - 1) / NTY;
+  ng.ntz = (bg.src.g.d0 + NTZ - 1) / NTZ;
+  const int near = bg.ntx * ng.nty * ng.ntz;
+  ng.items = near > bg.ntiles ? near : bg.ntiles;
+  return ng;
+}
+
+template <bool FIRST>
+__device__ __forceinline__ void exp_bwd_near(NearLds& L, int s, int tile,
+                                             const float* __restrict__ ut,
+                                             const float* __restrict__ gin,
+                                             float* __restrict__ gout, const NearGeom& ng,
+                                             float scale, float oscale) {
+  const Geom& g = ng.bg.src.g;
+  const int ox = (tile % ng.bg.ntx) * ETX;
+  const int oy = (tile / ng.bg.ntx) % ng.nty * NTY;
+  const int oz = tile / (ng.bg.ntx * ng.nty) * NTZ;
+  const size_t off = static_cast<size_t>(s) * 3 * g.V;
+  const int tid = threadIdx.x;
+  if (tid == 0) L.nonfinite = 0;
+  __syncthreads();
+  float pu[NNJ][3], pg[NNJ][3];
+#pragma unroll
+  for (int j = 0; j < NNJ; ++j) {
+    const int e = tid + j * ENT;
+    const int hz = e / (HHX * NHY), r = e - hz * (HHX * NHY);
+    const int hy = r / HHX, hx = r - hy * HHX;
+    const int z = oz - 1 + hz, y = oy - 1 + hy, x = ox - 1 + hx;
+    const bool in = e < NHP && z >= 0 && z < g.d0 && y >= 0 && y < g.d1 && x >= 0 && x < g.d2;
+    const uint32_t lin = in ? static_cast<uint32_t>((z * g.d1 + y) * g.d2 + x) << 2 : kNoAccess;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const size_t oc = off + static_cast<size_t>(c) * g.V;
+      pu[j][c] = load_masked(masked_in(ut + oc, static_cast<uint32_t>(g.V)), lin);
+      pg[j][c] = load_masked(masked_in(gin + oc, static_cast<uint32_t>(g.V)), lin);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NNJ; ++j) {
+    const int e = tid + j * ENT;
+    if (e >= NHP) continue;
+    const int hz = e / (HHX * NHY), r = e - hz * (HHX * NHY);
+    const int hy = r / HHX, hx = r - hy * HHX;
+    const float js = FIRST ? scale : 1.0f;
+    L.src4[e] = make_float4(hat_clamp(pu[j][0] * js, hat_range(oz - 1 + hz, g.d0)),
+                            hat_clamp(pu[j][1] * js, hat_range(oy - 1 + hy, g.d1)),
+                            hat_clamp(pu[j][2] * js, hat_range(ox - 1 + hx, g.d2)), pg[j][0]);
+    L.src2[e] = make_float2(pg[j][1], pg[j][2]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) L.uraw[c][e] = pu[j][c];
+    if (!__builtin_isfinite(pg[j][0] + pg[j][1] + pg[j][2])) L.nonfinite = 1;
+  }
+  __syncthreads();
+  const int lx = tid % ETX, ly = tid / ETX;
+  const int at = ly * HHX + lx;  // first of the sources around the first target
+  float acc[2][3] = {};
+  if (!L.nonfinite) {
+#pragma unroll
+    for (int k = 0; k < NHZ; ++k)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const float4 p = L.src4[at + (k * NHY + j) * HHX + i];
+          const float2 q = L.src2[at + (k * NHY + j) * HHX + i];
+          const float w = hat(p.y, 1 - j) * hat(p.z, 1 - i);
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            if (r + 1 - k < -1 || r + 1 - k > 1) continue;
+            const float wt = w * hat(p.x, r + 1 - k);
+            acc[r][0] = fmaf(wt, p.w, acc[r][0]);
+            acc[r][1] = fmaf(wt, q.x, acc[r][1]);
+            acc[r][2] = fmaf(wt, q.y, acc[r][2]);
+          }
+        }
+  } else {
+    // a gradient that is not finite reaches the eight corners of its cell
+    // (whatever their weight) and nothing else
+#pragma unroll 1
+    for (int e = 0; e < 9 * NHZ; ++e) {
+      const int k = e / 9, j = e / 3 % 3, i = e % 3;
+      const float4 p = L.src4[at + (k * NHY + j) * HHX + i];
+      const float2 q = L.src2[at + (k * NHY + j) * HHX + i];
+      const int o0 = (p.x < 0.0f || oz + k - 1 == g.d0 - 1) ? -1 : 0;
+      const int o1 = (p.y < 0.0f || oy + ly + j - 1 == g.d1 - 1) ? -1 : 0;
+      const int o2 = (p.z < 0.0f || ox + lx + i - 1 == g.d2 - 1) ? -1 : 0;
+      const int e1 = 1 - j - o1, e2 = 1 - i - o2;
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int e0 = r + 1 - k - o0;
+        if (((e0 | e1 | e2) & ~1) != 0) continue;
+        const float wt = corner_weight(e0, e1, e2, p.x - o0, p.y - o1, p.z - o2);
+        acc[r][0] += wt * p.w;
+        acc[r][1] += wt * q.x;
+        acc[r][2] += wt * q.y;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int z = oz + r, y = oy + ly, x = ox + lx;
+    // direct term (computed for ragged lanes too, from staged zeros)
+    const int own = at + ((r + 1) * NHY + 1) * HHX + 1;
+    const float4 p = L.src4[own];
+    const float2 q = L.src2[own];
+    const float js = FIRST ? scale : 1.0f;
+    const bool k0 = L.uraw[0][own] * js != p.x, k1 = L.uraw[1][own] * js != p.y,
+               k2 = L.uraw[2][own] * js != p.z;
+    const int o0 = (p.x < 0.0f || z == g.d0 - 1) ? 1 : 0;
+    const int o1 = (p.y < 0.0f || y == g.d1 - 1) ? 1 : 0;
+    const int o2 = (p.z < 0.0f || x == g.d2 - 1) ? 1 : 0;
+    const int pb = own - (o0 * NHY + o1) * HHX - o2;
+    const float gc[3] = {p.w, q.x, q.y};
+    float h[8];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float cv = L.uraw[c][pb + ((k >> 2) * NHY + ((k >> 1) & 1)) * HHX + (k & 1)];
+        h[k] = c == 0 ? gc[0] * cv : h[k] + gc[c] * cv;
+      }
+    const Tri t = tri_eval(h, p.x + o0, p.y + o1, p.z + o2);
+    if (z < g.d0 && y < g.d1 && x < g.d2) {
+      float* o = gout + off;
+      const uint32_t lin = static_cast<uint32_t>((z * g.d1 + y) * g.d2 + x);
+      st_at(o, lin, (acc[r][0] + gc[0] + (k0 ? 0.0f : t.d0 * js)) * oscale);
+      st_at(o + g.V, lin, (acc[r][1] + gc[1] + (k1 ? 0.0f : t.d1 * js)) * oscale);
+      st_at(o + 2 * static_cast<size_t>(g.V), lin,
+            (acc[r][2] + gc[2] + (k2 ? 0.0f : t.d2 * js)) * oscale);
+    }
+  }
+}
+
+union SmallBwdLds {
+  TiledBwdLds tiled;
+  NearLds near;
+};
+
+template <bool FIRST>
+__global__ __launch_bounds__(ENT) void k_exp_bwd_small(const float* __restrict__ ut,
+                                                       const float* __restrict__ gin,
+                                                       float* __restrict__ gout, NearGeom ng,
+                                                       float scale, float oscale,
+                                                       const int* __restrict__ boxes,
+                                                       const int* __restrict__ reach) {
+  __shared__ __align__(16) unsigned char lds[sizeof(SmallBwdLds)];
+  SmallBwdLds& L = *reinterpret_cast<SmallBwdLds*>(lds);
+  const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+  const int s = static_cast<int>(b / ng.items);
+  const int item = static_cast<int>(b - static_cast<uint32_t>(s) * ng.items);
+  const int* rc = reach + s * 8;
+  if (max(max(max(rc[0], rc[1]), max(rc[2], rc[3])), max(rc[4], rc[5])) <= 1) {
+    if (item < ng.bg.ntx * ng.nty * ng.ntz)
+      exp_bwd_near<FIRST>(L.near, s, item, ut, gin, gout, ng, scale, oscale);
+  } else if (item < ng.bg.ntiles) {
+    exp_bwd_tile<FIRST>(L.tiled, s, item, ut, gin, gout, ng.bg, scale, oscale, boxes, reach);
+  }
 }
 
 // Adjoint of one squaring step, marching, for a subject whose cell offsets
@@ -1436,9 +1621,10 @@ AuxPtrs aux_ptrs(int* aux, const TileGeom& tg, int n, int n_sq) {
 
 // One plane of a record tile (32 x 8 voxels, one per thread) of a squaring
 // step: the arithmetic of k_exp_fwd<FIRST, REC> with the corners read from
-// memory.  With REC the block merges its cell offsets into the tile's record
-// (global atomics on boxes initialised by k_box_init) and raises the
-// subject's reaches.  Blocks are (subject, tile, plane), so a small volume
+// memory.  With REC the block merges cell offsets beyond [-1, 0] into the
+// tile's record (which starts at that range) and the subject's reaches, which
+// count from 2 on: the atomics of every plane into its tile's record took as
+// long as the step itself (6.1 against 3.8 us at 4 x 32^3).  Blocks are (subject, tile, plane), so a small volume
 // gets eight times the blocks of the marching kernel and no serial planes.
 template <bool FIRST, bool REC>
 __device__ __forceinline__ void exp_fwd_plane_body(int (*red)[ENT / 64], uint32_t blk,
@@ -1509,27 +1695,29 @@ __device__ __forceinline__ void exp_fwd_plane_body(int (*red)[ENT / 64], uint32_
       int r = red[q][0];
       for (int i = 1; i < ENT / 64; ++i) r = q < 3 ? min(r, red[q][i]) : max(r, red[q][i]);
       int* bx = boxes + (static_cast<size_t>(s) * tg.ntiles + tile) * 8;
-      if (q < 3) {
+      if (q < 3 && r < -1) {
         atomicMin(bx + q, r);
-        if (-r > 0) atomicMax(reach + s * 8 + q, -r);
-      } else {
+        atomicMax(reach + s * 8 + q, -r);
+      } else if (q >= 3 && r > 0) {
         atomicMax(bx + q, r);
-        if (r + 1 > 0) atomicMax(reach + s * 8 + q, r + 1);
+        atomicMax(reach + s * 8 + q, r + 1);
       }
     }
     __syncthreads();  // `red` is rewritten by the block's next plane
   }
 }
 
-// Record boxes of `count` tiles set to the empty box (min INT_MAX, max
-// INT_MIN), before planes merge into them.
-__global__ __launch_bounds__(ENT) void k_box_init(int* __restrict__ boxes, long long count) {
+// Value that entry e of a record box starts at before planes merge into it:
+// offsets in [-1, 0].
+__device__ __forceinline__ int box_start(int e) { return e < 3 ? -1 : 0; }
+
+// Boxes of `nbox` entries, followed by nreach zeroed reaches.
+__global__ __launch_bounds__(ENT) void k_aux_init(int* __restrict__ aux, long long nbox,
+                                                  long long nreach) {
   const long long stride = static_cast<long long>(gridDim.x) * ENT;
-  for (long long i = static_cast<long long>(blockIdx.x) * ENT + threadIdx.x; i < count * 8;
-       i += stride) {
-    const int e = static_cast<int>(i & 7);
-    boxes[i] = e < 3 ? INT_MAX : (e < 6 ? INT_MIN : 0);
-  }
+  for (long long i = static_cast<long long>(blockIdx.x) * ENT + threadIdx.x; i < nbox + nreach;
+       i += stride)
+    aux[i] = i < nbox ? box_start(static_cast<int>(i & 7)) : 0;
 }
 
 template <bool FIRST, bool REC>
@@ -1625,8 +1813,7 @@ __global__ __launch_bounds__(ENT) void k_iter_fused(IterArgs a) {
     const long long nb = static_cast<long long>(a.box_stride) * a.n_sq;
     for (long long i = static_cast<long long>(blockIdx.x) * ENT + threadIdx.x; i < nb;
          i += static_cast<long long>(G) * ENT) {
-      const int e = static_cast<int>(i & 7);
-      a.boxes[i] = e < 3 ? INT_MAX : (e < 6 ? INT_MIN : 0);
+      a.boxes[i] = box_start(static_cast<int>(i & 7));
     }
   }
   grid_barrier(a.bar, a.err, ++nbar, a.ticks);
@@ -1663,11 +1850,15 @@ __global__ __launch_bounds__(ENT) void k_iter_fused(IterArgs a) {
     const float* ut = (t == 0) ? a.v : a.ckpt + static_cast<size_t>(t - 1) * fs;
     const int* bx = a.boxes + a.box_stride * t;
     const int* rc = a.reach + a.reach_stride * t;
-    if (t == 0)
-      exp_bwd_tiled_body<true, true>(L, blockIdx.x, G, ut, gin, gout, a.bg, a.scale, a.scale, bx,
-                                     rc);
-    else
-      exp_bwd_tiled_body<false, true>(L, blockIdx.x, G, ut, gin, gout, a.bg, 1.0f, 1.0f, bx, rc);
+    for (uint32_t b = blockIdx.x; b < a.bg.total; b += G) {
+      const uint32_t bid = xcd_remap(b, a.bg.total);
+      const int sub = static_cast<int>(bid / a.bg.ntiles);
+      const int tile = static_cast<int>(bid - static_cast<uint32_t>(sub) * a.bg.ntiles);
+      if (t == 0)
+        exp_bwd_tile<true>(L, sub, tile, ut, gin, gout, a.bg, a.scale, a.scale, bx, rc);
+      else
+        exp_bwd_tile<false>(L, sub, tile, ut, gin, gout, a.bg, 1.0f, 1.0f, bx, rc);
+    }
     grid_barrier(a.bar, a.err, ++nbar, a.ticks);
     gin = gout;
   }
@@ -1712,9 +1903,9 @@ int march_tz(const TileGeom& tg, int n) {
 }
 
 // The other shape of the squaring steps and their adjoint: one plane of a
-// tile per block (k_exp_fwd_planes) and the tiled adjoint for every subject,
-// no marching.  It wins on small volumes, where the marching kernels' serial
-// planes are the whole cost (4 x 32^3: 0.78 ms per sweep against 1.60).
+// tile per block (k_exp_fwd_planes) and an adjoint tile per block
+// (k_exp_bwd_small), no marching.  It wins on small volumes, where the marching kernels' serial
+// planes are the whole cost (4 x 32^3: half the time per sweep).
 // Untuned, it is taken when the marching grid would hold fewer than four
 // blocks per CU even with 8-plane chunks.
 bool plane_mode(const Geom& g, int n) {
@@ -1739,18 +1930,19 @@ void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, co
   const AuxPtrs ap = aux_ptrs(aux, tg, n, n_sq);
   const bool planes = plane_mode(g, n);
   // the reaches are running maxima: start them at zero (all-zero bits); the
-  // planes kernel merges into its boxes, which start empty
-  if (aux) {
+  // planes kernel merges into its boxes too
+  if (aux && planes) {
+    const long long nbox = static_cast<long long>(ap.box_stride) * n_sq;
+    const long long nreach = static_cast<long long>(ap.reach_stride) * n_sq;
+    prof_begin(st, KC_FILL);
+    hipLaunchKernelGGL(k_aux_init, dim3(static_cast<uint32_t>(
+                                       (nbox + nreach) / ENT + 1 < 65536 ? (nbox + nreach) / ENT + 1
+                                                                         : 65536)),
+                       dim3(ENT), 0, st, aux, nbox, nreach);
+    prof_end(st, KC_FILL);
+  } else if (aux) {
     launch_fill_f32(reinterpret_cast<float*>(ap.reach),
                     static_cast<long long>(ap.reach_stride) * n_sq, 0.0f, st);
-    if (planes) {
-      const long long nbox = static_cast<long long>(ap.box_stride / 8) * n_sq;
-      prof_begin(st, KC_FILL);
-      hipLaunchKernelGGL(k_box_init, dim3(static_cast<uint32_t>(
-                                         nbox * 8 / ENT + 1 < 65536 ? nbox * 8 / ENT + 1 : 65536)),
-                         dim3(ENT), 0, st, ap.boxes, nbox);
-      prof_end(st, KC_FILL);
-    }
   }
   // Exp(-v) negates the scaled field of the first step (exact)
   const float scale = negate ? -ldexpf(1.0f, -n_sq) : ldexpf(1.0f, -n_sq);
@@ -1818,13 +2010,14 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, bool first,
                      hipStream_t st) {
   prof_begin(st, KC_EXP_BWD);
   if (planes) {
-    // every subject on the tiled adjoint
+    const NearGeom ng = make_near(bg);
+    const dim3 grid(static_cast<uint32_t>(ng.items) * (bg.total / bg.ntiles));
     if (first)
-      hipLaunchKernelGGL((k_exp_bwd<true, true>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
-                         gout, bg, scale, scale, bx, rc);
+      hipLaunchKernelGGL((k_exp_bwd_small<true>), grid, dim3(ENT), 0, st, ut, gin, gout, ng, scale,
+                         scale, bx, rc);
     else
-      hipLaunchKernelGGL((k_exp_bwd<false, true>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
-                         gout, bg, 1.0f, 1.0f, bx, rc);
+      hipLaunchKernelGGL((k_exp_bwd_small<false>), grid, dim3(ENT), 0, st, ut, gin, gout, ng, 1.0f,
+                         1.0f, bx, rc);
     prof_end(st, KC_EXP_BWD);
     return;
   }
@@ -1836,14 +2029,14 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, bool first,
                        scale, scale, rc);
     hipLaunchKernelGGL((k_exp_bwd_march2<true>), dim3(march2_grid(m)), dim3(ENT), 0, st, ut, gin,
                        gout, m, scale, scale, rc);
-    hipLaunchKernelGGL((k_exp_bwd<true, false>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
+    hipLaunchKernelGGL((k_exp_bwd<true>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
                        gout, bg, scale, scale, bx, rc);
   } else {
     hipLaunchKernelGGL((k_exp_bwd_hat<false>), dim3(hg.total), dim3(ENT), 0, st, ut, gin, gout, hg,
                        1.0f, 1.0f, rc);
     hipLaunchKernelGGL((k_exp_bwd_march2<false>), dim3(march2_grid(m)), dim3(ENT), 0, st, ut, gin,
                        gout, m, 1.0f, 1.0f, rc);
-    hipLaunchKernelGGL((k_exp_bwd<false, false>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
+    hipLaunchKernelGGL((k_exp_bwd<false>), dim3(bwd_grid(bg)), dim3(BNT), 0, st, ut, gin,
                        gout, bg, 1.0f, 1.0f, bx, rc);
   }
   prof_end(st, KC_EXP_BWD);
