@@ -179,10 +179,6 @@ __global__ __launch_bounds__(ENT) void k_exp_rec(const float* __restrict__ v,
 // with a one-voxel halo in d1 and d2 lives in LDS; the next plane is loaded
 // into registers while the current one is computed, so every value is read
 // from memory once and loads overlap compute.
-constexpr int MHX = ETX + 2, MHY = ETY + 2;  // staged plane with halo
-constexpr int MHP = MHX * MHY;               // 340 positions
-constexpr int MNJ = (MHP + ENT - 1) / ENT;   // positions per thread (2)
-
 struct MarchGeom {
   TileGeom rec;  // record tiling (same 32 x 8 columns, 8 planes per record)
   int nzc, tz;   // chunks along d0 and their length (a multiple of ETZ)
@@ -217,152 +213,234 @@ __device__ __forceinline__ MarchId march_id_at(const MarchGeom& m, uint32_t b) {
   return id;
 }
 
-__device__ __forceinline__ MarchId march_id(const MarchGeom& m) {
-  return march_id_at(m, xcd_remap(blockIdx.x, m.total));
-}
+// Columns of the marching squaring step and of its reach-1 adjoint: 32 x 16,
+// two adjacent rows per thread, a one-voxel halo staged in LDS.
+constexpr int HTY = 16;
+constexpr int HHX = ETX + 2, HHY = HTY + 2;    // staged plane with halo: 34 x 18
+constexpr int HHP = HHX * HHY;                 // 612 positions
+constexpr int HRING = HHP - 2 * ENT;           // halo positions (100)
+// One plane of the ring of u, its components HHP apart, padded to a multiple of
+// the 64 LDS banks: lanes of a row whose cells lie in different planes then
+// read different banks.
+constexpr int HSLOT = (3 * HHP + 63) / 64 * 64;
 
-// Halo positions of one plane handled by this thread: in-plane offset of the
-// (clamped) voxel, and whether the unclamped voxel exists.
-struct HaloPos {
-  int off[MNJ];
-  bool use[MNJ];     // position index < MHP
-  bool inside[MNJ];  // the voxel is inside the volume (d1, d2)
-  int y[MNJ], x[MNJ];
+struct HatGeom {
+  Geom g;
+  int ntx, nty, nzc, tz;  // columns and chunks along d0
+  uint32_t total;
 };
 
-__device__ __forceinline__ HaloPos halo_pos(const Geom& g, int oy, int ox) {
-  HaloPos h;
-#pragma unroll
-  for (int j = 0; j < MNJ; ++j) {
-    const int e = threadIdx.x + j * ENT;
-    h.use[j] = e < MHP;
-    const int hy = e / MHX, hx = e - hy * MHX;
-    const int y = oy - 1 + hy, x = ox - 1 + hx;
-    h.y[j] = y;
-    h.x[j] = x;
-    h.inside[j] = y >= 0 && y < g.d1 && x >= 0 && x < g.d2;
-    h.off[j] = min(max(y, 0), g.d1 - 1) * g.d2 + min(max(x, 0), g.d2 - 1);
-  }
+HatGeom make_hat(const TileGeom& tg, int tz) {
+  HatGeom h;
+  h.g = tg.g;
+  h.ntx = tg.ntx;
+  h.nty = (tg.g.d1 + HTY - 1) / HTY;
+  h.tz = tz;
+  h.nzc = (tg.g.d0 + tz - 1) / tz;
+  h.total = static_cast<uint32_t>(h.ntx) * h.nty * h.nzc * (tg.total / tg.ntiles);
   return h;
 }
 
-// Forward squaring step, marching.  REC: also write the per-tile records.
-template <bool FIRST, bool REC>
+// Halo-ring position (hy, hx) of thread tid < HRING in the staged plane.
+__device__ __forceinline__ void ring_position(int tid, int& hy, int& hx) {
+  if (tid < 2 * HHX) {
+    hy = tid < HHX ? 0 : HHY - 1;
+    hx = tid < HHX ? tid : tid - HHX;
+  } else {
+    const int q = min(tid - 2 * HHX, 2 * HTY - 1);
+    hy = 1 + (q >> 1);
+    hx = (q & 1) * (HHX - 1);
+  }
+}
+
+// As many (discarded) stores after the loads of the loop's first plane as every
+// step issues after its loads, so that the wait at the head of the loop counts
+// the same on both ways in and leaves the stores in flight.
+__device__ __forceinline__ void discarded_stores(const MaskedOut (&out)[3]) {
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) store_masked(out[k % 3], 0u, 0.0f, false);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Forward squaring step, marching.  REC: also write the records of the block's
+// two record tiles (rows 0-7 and 8-15) per 8 planes.
+//
+// A stream of 24 B per voxel (read u_t, write u_{t+1}) whose 24 corner reads
+// come from LDS; bound by the memory system (1.4x the input fetched, the halo
+// lines that L2 no longer holds; neither fewer instructions nor a second plane
+// in flight changed its time).  16 x 160 x 192 x 224: 0.60 ms, 4.4 TB/s; on
+// 32 x 8 columns with every cell formed in full 0.65.  Away from the faces and with |u| < 1 a voxel's cell is at
+// -1 or 0 by the sign of u; other voxels take the general cell, with corners
+// from memory where they leave the staged planes.  Records start at offsets
+// [-1, 0] and grow with those other voxels only.
+template <bool FIRST, bool REC, bool STREAM>
 __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
-                                                 float* __restrict__ dst, MarchGeom m,
+                                                 float* __restrict__ dst, HatGeom m, TileGeom rec,
                                                  float scale, int* __restrict__ boxes,
                                                  int* __restrict__ reach) {
-  __shared__ float ring[3][3][MHP];  // [plane slot][component][position]
+  __shared__ float ring[3 * HSLOT];
   __shared__ int red[6][ENT / 64];
-  const Geom& g = m.rec.g;
-  const MarchId id = march_id(m);
-  const size_t off = static_cast<size_t>(id.s) * 3 * g.V;
-  const float* f = src + off;
-  float* o = dst + off;
-  const int lx = threadIdx.x % ETX, ly = threadIdx.x / ETX;
-  const HaloPos hp = halo_pos(g, id.oy, id.ox);
-  // the next plane in registers (planes past the chunk are loaded clamped)
-  const float* fc[3] = {f, f + g.V, f + 2 * static_cast<size_t>(g.V)};
-  float pre[MNJ][3];
-  auto load_plane = [&](int z) {
-    const int zc = min(max(z, 0), g.d0 - 1);
+  const Geom& g = m.g;
+  uint32_t b = xcd_remap(blockIdx.x, m.total);
+  const int tx = static_cast<int>(b % m.ntx);
+  b /= m.ntx;
+  const int ty = static_cast<int>(b % m.nty);
+  b /= m.nty;
+  const int z0 = static_cast<int>(b % m.nzc) * m.tz, z1 = min(z0 + m.tz, g.d0);
+  const int s = static_cast<int>(b / m.nzc);
+  const int ox = tx * ETX, oy = ty * HTY;
+  const size_t off = static_cast<size_t>(s) * 3 * g.V;
+  MaskedOut out[3];
+  MaskedIn in[3];
 #pragma unroll
-    for (int j = 0; j < MNJ; ++j)
-      if (hp.use[j]) {
-        const uint32_t lin = static_cast<uint32_t>(zc * g.plane + hp.off[j]);
+  for (int c = 0; c < 3; ++c) {
+    in[c] = masked_in(src + off + static_cast<size_t>(c) * g.V, static_cast<uint32_t>(g.V));
+    out[c] = masked_out(dst + off + static_cast<size_t>(c) * g.V, static_cast<uint32_t>(g.V));
+  }
+  const int tid = threadIdx.x, lx = tid % ETX, ry = tid / ETX;
+  const int x2 = ox + lx, y1 = oy + 2 * ry;
+  const int at = (2 * ry + 1) * HHX + lx + 1;  // staged position of the first voxel
+  int pr;
+  uint32_t poff[3];
+  {
+    int hy, hx;
+    ring_position(tid, hy, hx);
+    pr = hy * HHX + hx;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) pre[j][c] = ld_at(fc[c], lin);
-      }
+    for (int j = 0; j < 3; ++j) {
+      const int y = j < 2 ? y1 + j : oy - 1 + hy, x = j < 2 ? x2 : ox - 1 + hx;
+      const bool inside = y >= 0 && y < g.d1 && x >= 0 && x < g.d2 && (j < 2 || tid < HRING);
+      poff[j] = inside ? static_cast<uint32_t>(y * g.d2 + x) << 2 : kNoAccess;
+    }
+  }
+  const bool rg = tid < HRING;
+  // the column or its halo touches a face of the volume in d1 or d2
+  const bool face = oy == 0 || ox == 0 || oy + HTY >= g.d1 - 1 || ox + ETX >= g.d2 - 1;
+  float pre[3][3];
+  auto load_plane = [&](int z) {  // planes outside the volume are loaded clamped
+    const uint32_t zo = static_cast<uint32_t>(min(max(z, 0), g.d0 - 1) * g.plane) << 2;
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) pre[j][c] = load_masked(in[c], zo + poff[j]);
   };
-  auto store_plane = [&](int z) {
-    const int sl = (z + 3) % 3;
+  auto stage = [&](int z) {
+    float* r = ring + (z + 3) % 3 * HSLOT;
 #pragma unroll
-    for (int j = 0; j < MNJ; ++j)
-      if (hp.use[j]) {
-        const int e = threadIdx.x + j * ENT;
-        ring[sl][0][e] = pre[j][0];
-        ring[sl][1][e] = pre[j][1];
-        ring[sl][2][e] = pre[j][2];
-      }
+    for (int c = 0; c < 3; ++c) {
+      r[c * HHP + at] = pre[0][c];
+      r[c * HHP + at + HHX] = pre[1][c];
+      if (rg) r[c * HHP + pr] = pre[2][c];
+    }
   };
-  load_plane(id.z0 - 1);
-  store_plane(id.z0 - 1);
-  load_plane(id.z0);
-  store_plane(id.z0);
-  load_plane(id.z0 + 1);
-  const int x2 = id.ox + lx, x1 = id.oy + ly;
-  const bool colv = (x2 < g.d2) && (x1 < g.d1);
-  const int own = (ly + 1) * MHX + lx + 1;
-  int mn0 = INT_MAX, mn1 = INT_MAX, mn2 = INT_MAX, mx0 = INT_MIN, mx1 = INT_MIN, mx2 = INT_MIN;
+  load_plane(z0 - 1);
+  stage(z0 - 1);
+  load_plane(z0);
+  stage(z0);
+  load_plane(z0 + 1);
+  discarded_stores(out);
+  int mn[3] = {-1, -1, -1}, mx[3] = {0, 0, 0};
   int rmax = 0;
-  for (int z = id.z0; z < id.z1; ++z) {
-    store_plane(z + 1);
-    __syncthreads();
+  int z = z0;
+  do {  // (a loop whose first pass is conditional would let the loads above sink into it)
+    stage(z + 1);
     load_plane(z + 2);
-    if (colv) {
-      const int sz = z % 3;
-      float u0 = ring[sz][0][own], u1 = ring[sz][1][own], u2 = ring[sz][2][own];
-      if (FIRST) {
-        u0 *= scale;
-        u1 *= scale;
-        u2 *= scale;
+    __syncthreads();
+    const float* r0 = ring;
+    const int slm = (z + 2) % 3 * HSLOT, slc = z % 3 * HSLOT, slp = (z + 1) % 3 * HSLOT;
+    const bool edge = face || z == 0 || z >= g.d0 - 1;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int own = at + r * HHX;
+      float u[3], res[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        u[c] = r0[slc + c * HHP + own];
+        if (FIRST) u[c] *= scale;
       }
-      const BorderCell bc = border_cell(g, z, x1, x2, u0, u1, u2);
-      const int c0 = bc.i0 - z + 1, c1 = bc.i1 - id.oy + 1, c2 = bc.i2 - id.ox + 1;
-      float r[3];
-      if (c0 >= 0 && c0 <= 1 && c1 >= 0 && c1 + 1 < MHY && c2 >= 0 && c2 + 1 < MHX) {
-        // ring slots of planes i0 and i0 + 1, i0 in {z - 1, z}: uniform choices
-        const int sa = c0 ? sz : (z + 2) % 3, sb = c0 ? (z + 1) % 3 : sz;
-        const int pb = c1 * MHX + c2;
+      const bool live = x2 < g.d2 && y1 + r < g.d1;
+      const bool near = !edge && fabsf(u[0]) < 1.0f && fabsf(u[1]) < 1.0f && fabsf(u[2]) < 1.0f;
+      bool lo0 = u[0] < 0.0f, lo1 = u[1] < 0.0f, lo2 = u[2] < 0.0f;
+      float t0 = u[0] + (lo0 ? 1.0f : 0.0f), t1 = u[1] + (lo1 ? 1.0f : 0.0f),
+            t2 = u[2] + (lo2 ? 1.0f : 0.0f);
+      int pb = own + (lo1 ? -HHX : 0) + (lo2 ? -1 : 0);
+      bool ringed = near || !live;
+      int base = 0;
+      if (!near && live) {
+        const BorderCell bc = border_cell(g, z, y1 + r, x2, u[0], u[1], u[2]);
+        const int c0 = bc.i0 - z, c1 = bc.i1 - oy + 1, c2 = bc.i2 - ox + 1;
+        ringed = c0 >= -1 && c0 <= 0 && c1 >= 0 && c1 + 1 < HHY && c2 >= 0 && c2 + 1 < HHX;
+        lo0 = c0 < 0;
+        pb = c1 * HHX + c2;
+        base = bc.base;
+        t0 = bc.t0;
+        t1 = bc.t1;
+        t2 = bc.t2;
+        if (REC) {
+          mn[0] = min(mn[0], c0);
+          mn[1] = min(mn[1], bc.i1 - (y1 + r));
+          mn[2] = min(mn[2], bc.i2 - x2);
+          mx[0] = max(mx[0], c0);
+          mx[1] = max(mx[1], bc.i1 - (y1 + r));
+          mx[2] = max(mx[2], bc.i2 - x2);
+        }
+      }
+      if (ringed) {
+        const float* ra = r0 + (pb + (lo0 ? slm : slc));
+        const float* rb = r0 + (pb + (lo0 ? slc : slp));
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          float cv[8];
-          cv[0] = ring[sa][c][pb];
-          cv[1] = ring[sa][c][pb + 1];
-          cv[2] = ring[sa][c][pb + MHX];
-          cv[3] = ring[sa][c][pb + MHX + 1];
-          cv[4] = ring[sb][c][pb];
-          cv[5] = ring[sb][c][pb + 1];
-          cv[6] = ring[sb][c][pb + MHX];
-          cv[7] = ring[sb][c][pb + MHX + 1];
-          r[c] = tri_value(cv, bc.t0, bc.t1, bc.t2);
+          const float cv[8] = {ra[c * HHP],       ra[c * HHP + 1],
+                               ra[c * HHP + HHX], ra[c * HHP + HHX + 1],
+                               rb[c * HHP],       rb[c * HHP + 1],
+                               rb[c * HHP + HHX], rb[c * HHP + HHX + 1]};
+          res[c] = tri_value(cv, t0, t1, t2);
         }
       } else {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           float cv[8];
-          corners_border(fc[c], g, bc.base, cv);
-          r[c] = tri_value(cv, bc.t0, bc.t1, bc.t2);
+          corners_border(src + off + c * static_cast<size_t>(g.V), g, base, cv);
+          res[c] = tri_value(cv, t0, t1, t2);
         }
       }
-      if (FIRST) {
-        r[0] *= scale;
-        r[1] *= scale;
-        r[2] *= scale;
-      }
-      const uint32_t lin = static_cast<uint32_t>(z * g.plane + x1 * g.d2 + x2);
-      st_at(o, lin, u0 + r[0]);
-      st_at(o + g.V, lin, u1 + r[1]);
-      st_at(o + 2 * static_cast<size_t>(g.V), lin, u2 + r[2]);
-      if (REC) {
-        mn0 = min(mn0, bc.i0 - z);
-        mn1 = min(mn1, bc.i1 - x1);
-        mn2 = min(mn2, bc.i2 - x2);
-        mx0 = max(mx0, bc.i0 - z);
-        mx1 = max(mx1, bc.i1 - x1);
-        mx2 = max(mx2, bc.i2 - x2);
-      }
+      const uint32_t lin = static_cast<uint32_t>(z * g.plane + (y1 + r) * g.d2 + x2);
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        store_masked<STREAM>(out[c], lin, FIRST ? fmaf(res[c], scale, u[c]) : u[c] + res[c], live);
     }
-    if (REC && ((z + 1) % ETZ == 0 || z + 1 == id.z1)) {
-      const int tile = ((z / ETZ) * m.rec.nty + id.ty) * m.rec.ntx + id.tx;
-      write_record(mn0, mn1, mn2, mx0, mx1, mx2, red, boxes, id.s, tile, m.rec.ntiles, rmax);
-      mn0 = mn1 = mn2 = INT_MAX;
-      mx0 = mx1 = mx2 = INT_MIN;
+    if (REC && ((z + 1) % ETZ == 0 || z + 1 == z1)) {
+      // the box entries over each half's two waves; thread q of 12 finishes
+      // entry q % 6 of half q / 6 and folds its reach into a running maximum
+      // (issued once per block)
+      const int lane = tid & 63, w = tid >> 6;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int a = wave_min(mn[d]), c = wave_max(mx[d]);
+        if (lane == 0) {
+          red[d][w] = a;
+          red[3 + d][w] = c;
+        }
+        mn[d] = -1;
+        mx[d] = 0;
+      }
+      __syncthreads();
+      if (tid < 12) {
+        const int q = tid % 6, hf = tid / 6;
+        const int a = red[q][2 * hf], c = red[q][2 * hf + 1];
+        const int v = q < 3 ? min(a, c) : max(a, c);
+        if (oy + 8 * hf < g.d1) {
+          const int tile = ((z / ETZ) * rec.nty + 2 * ty + hf) * rec.ntx + tx;
+          boxes[(static_cast<size_t>(s) * rec.ntiles + tile) * 8 + q] = v;
+          rmax = max(rmax, q < 3 ? -v : v + 1);
+        }
+      }
     } else {
       __syncthreads();
     }
-  }
-  if (REC) flush_reach(rmax, reach, id.s);
+  } while (++z < z1);
+  if (REC && tid < 12 && rmax > 1) atomicMax(reach + s * 8 + tid % 6, rmax);
 }
 
 // Adjoint tiles: 4 (d0) x 4 (d1) x 32 (d2) output voxels, two per thread.
@@ -667,30 +745,8 @@ __device__ __forceinline__ void exp_bwd_tile(TiledBwdLds& L, int s, int tile,
 // next to it must not see 0 * g when g is not finite.  A block that meets
 // such a g says so in its subject's record (kNonFinite), and the tiled kernel,
 // launched after this one, then computes that subject again.
-constexpr int HTY = 16;                        // rows of a column (two per thread)
-constexpr int HHX = ETX + 2, HHY = HTY + 2;    // staged plane with halo: 34 x 18
-constexpr int HHP = HHX * HHY;                 // 612 positions
-constexpr int HRING = HHP - 2 * ENT;           // halo positions (100)
-
-struct HatGeom {
-  Geom g;
-  int ntx, nty, nzc, tz;  // columns and chunks along d0
-  uint32_t total;
-};
-
-HatGeom make_hat(const TileGeom& tg, int tz) {
-  HatGeom h;
-  h.g = tg.g;
-  h.ntx = tg.ntx;
-  h.nty = (tg.g.d1 + HTY - 1) / HTY;
-  h.tz = tz;
-  h.nzc = (tg.g.d0 + tz - 1) / tz;
-  h.total = static_cast<uint32_t>(h.ntx) * h.nty * h.nzc * (tg.total / tg.ntiles);
-  return h;
-}
-
 struct HatLds {
-  float uring[3][3][HHP];  // u_t of planes q-2, q-1, q (slot p % 3)
+  float uring[3 * HSLOT];  // u_t of planes q-2, q-1, q (slot p % 3)
   float4 src4[HHP];        // plane q: clamped u (scaled in the first step), g0
   float2 src2[HHP];        // g1, g2
   int stop;                // a cell beyond reach 1 was staged
@@ -755,7 +811,7 @@ __device__ __forceinline__ float hat_clamp(float u, uint32_t range) {
 // so a subject with a reach of 4 or more there is marked without a try.  (A
 // voxel next to a face that points outwards by more than one voxel is marked
 // too, though its clamped cell is within reach: the tiled kernel takes it.)
-template <bool FIRST, bool CHECK>
+template <bool FIRST, bool CHECK, bool STREAM>
 __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict__ ut,
                                                         const float* __restrict__ gin,
                                                         float* __restrict__ gout, HatGeom m,
@@ -802,14 +858,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
   uint32_t prange[3];     // clamping ranges along d2 and d1
   {
     int hy, hx;
-    if (tid < 2 * HHX) {
-      hy = tid < HHX ? 0 : HHY - 1;
-      hx = tid < HHX ? tid : tid - HHX;
-    } else {
-      const int q = min(tid - 2 * HHX, 2 * HTY - 1);
-      hy = 1 + (q >> 1);
-      hx = (q & 1) * (HHX - 1);
-    }
+    ring_position(tid, hy, hx);
     pr = hy * HHX + hx;
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
@@ -857,7 +906,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
       float u[3] = {pu[j][0], pu[j][1], pu[j][2]};
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        L.uring[sl][c][e] = u[c];
+        L.uring[sl * HSLOT + c * HHP + e] = u[c];
         if (FIRST) u[c] *= scale;
       }
       if (face || z <= 1 || z >= g.d0 - 2) {
@@ -873,16 +922,12 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
   };
 
   load_plane(z0 - 1);
-  // as many (discarded) stores after the first loads as every step issues, so
-  // that the loop's first wait counts the same on both ways in
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) store_masked(out[c], 0u, 0.0f, false);
+  discarded_stores(out);
   // twice the partial sums of the targets of planes q - 1 and q
   float accA[2][3] = {}, accB[2][3] = {};
   float og[2][3] = {};  // g of the targets of plane q - 1
-  for (int q = z0 - 1; q <= z1; ++q) {
+  int q = z0 - 1;
+  do {
     stage(q);
     load_plane(q + 1);
     __syncthreads();
@@ -895,8 +940,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
     asm volatile("" : "+v"(at));
     if (p >= z0) {
       // ring slots (as offsets) of planes p-1, p, p+1
-      constexpr int kSlot = 3 * HHP;
-      const int slm = (p + 2) % 3 * kSlot, slc = p % 3 * kSlot, slp = (p + 1) % 3 * kSlot;
+      const int slm = (p + 2) % 3 * HSLOT, slc = p % 3 * HSLOT, slp = (p + 1) % 3 * HSLOT;
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         // direct term: J^T g = gradient of the interpolant of g . u at the
@@ -906,7 +950,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
         bool lo[3], kl[3] = {false, false, false};  // cell below x; clamped
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          u[c] = (&L.uring[0][0][0])[slc + c * HHP + own];
+          u[c] = L.uring[slc + c * HHP + own];
           if (FIRST) u[c] *= scale;
           lo[c] = u[c] < 0.0f;
         }
@@ -926,8 +970,8 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
                     f2 = u[2] + (lo[2] ? 1.0f : 0.0f);
         // one component's corners: rows of planes i0 and i0 + 1
         const int pb = own + (lo[1] ? -HHX : 0) + (lo[2] ? -1 : 0);
-        const float* ra = &L.uring[0][0][0] + (pb + (lo[0] ? slm : slc));
-        const float* rb = &L.uring[0][0][0] + (pb + (lo[0] ? slc : slp));
+        const float* ra = L.uring + (pb + (lo[0] ? slm : slc));
+        const float* rb = L.uring + (pb + (lo[0] ? slc : slp));
         float h[8];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -965,13 +1009,13 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
       const bool on = p >= z0 && x2 < g.d2 && y1 + r < g.d1;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        store_masked(out[c], lin, (accA[r][c] + (sa[r][c] - ss[r][c])) * os, on);
+        store_masked<STREAM>(out[c], lin, (accA[r][c] + (sa[r][c] - ss[r][c])) * os, on);
         accA[r][c] = fmaf(2.0f, s0[r][c] - sa[r][c], accB[r][c]);
         accB[r][c] = sa[r][c] + ss[r][c];
       }
     }
     __syncthreads();
-  }
+  } while (++q <= z1);
   if (bad) reach[s * 8 + kNonFinite] = 1;
 }
 
@@ -1948,6 +1992,47 @@ bool plane_mode(const Geom& g, int n) {
   return march_blocks < 1024;
 }
 
+namespace {
+
+// One marching squaring step (records when bx is given).
+template <bool FIRST, bool REC>
+void launch_exp_fwd_r(const float* src, float* dst, const HatGeom& hg, const TileGeom& tg,
+                      float scale, int* bx, int* rc, hipStream_t st) {
+  const size_t out = static_cast<size_t>(tg.total / tg.ntiles) * 3 * tg.g.V * sizeof(float);
+  if (out > kStreamBytes)
+    hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, true>), dim3(hg.total), dim3(ENT), 0, st, src, dst,
+                       hg, tg, scale, bx, rc);
+  else
+    hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, false>), dim3(hg.total), dim3(ENT), 0, st, src, dst,
+                       hg, tg, scale, bx, rc);
+}
+
+void launch_exp_fwd(const float* src, float* dst, bool first, const HatGeom& hg,
+                    const TileGeom& tg, float scale, int* bx, int* rc, hipStream_t st) {
+  if (first && bx)
+    launch_exp_fwd_r<true, true>(src, dst, hg, tg, scale, bx, rc, st);
+  else if (first)
+    launch_exp_fwd_r<true, false>(src, dst, hg, tg, scale, bx, rc, st);
+  else if (bx)
+    launch_exp_fwd_r<false, true>(src, dst, hg, tg, scale, bx, rc, st);
+  else
+    launch_exp_fwd_r<false, false>(src, dst, hg, tg, scale, bx, rc, st);
+}
+
+// The reach-1 adjoint of one step (check: no records were taken).
+template <bool FIRST, bool CHECK>
+void launch_hat_r(const float* ut, const float* gin, float* gout, const HatGeom& hg, int n,
+                  float scale, int* rc, const int* later, hipStream_t st) {
+  if (static_cast<size_t>(n) * 3 * hg.g.V * sizeof(float) > kStreamBytes)
+    hipLaunchKernelGGL((k_exp_bwd_hat<FIRST, CHECK, true>), dim3(hg.total), dim3(ENT), 0, st, ut,
+                       gin, gout, hg, scale, scale, rc, later);
+  else
+    hipLaunchKernelGGL((k_exp_bwd_hat<FIRST, CHECK, false>), dim3(hg.total), dim3(ENT), 0, st, ut,
+                       gin, gout, hg, scale, scale, rc, later);
+}
+
+}  // namespace
+
 void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, const Geom& g, int n,
                  int n_sq, hipStream_t st, bool negate) {
   const size_t fs = static_cast<size_t>(n) * 3 * g.V;
@@ -1958,7 +2043,7 @@ void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, co
     return;
   }
   const TileGeom tg = make_tiles(g, n);
-  const MarchGeom m = make_march(tg, n, march_tz(tg, n));
+  const HatGeom hg = make_hat(tg, march_tz(tg, n));
   const AuxPtrs ap = aux_ptrs(aux, tg, n, n_sq);
   const bool planes = plane_mode(g, n);
   // the reaches are running maxima: start them at zero (all-zero bits); the
@@ -2004,20 +2089,8 @@ void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, co
       else
         hipLaunchKernelGGL((k_exp_fwd_planes<false, false>), grid, dim3(ENT), 0, st, src, dst,
                            tg, 1.0f, bx, rc);
-    } else if (t == 0) {
-      if (aux)
-        hipLaunchKernelGGL((k_exp_fwd<true, true>), dim3(m.total), dim3(ENT), 0, st, src, dst, m,
-                           scale, bx, rc);
-      else
-        hipLaunchKernelGGL((k_exp_fwd<true, false>), dim3(m.total), dim3(ENT), 0, st, src, dst, m,
-                           scale, bx, rc);
     } else {
-      if (aux)
-        hipLaunchKernelGGL((k_exp_fwd<false, true>), dim3(m.total), dim3(ENT), 0, st, src, dst, m,
-                           1.0f, bx, rc);
-      else
-        hipLaunchKernelGGL((k_exp_fwd<false, false>), dim3(m.total), dim3(ENT), 0, st, src, dst,
-                           m, 1.0f, bx, rc);
+      launch_exp_fwd(src, dst, t == 0, hg, tg, t == 0 ? scale : 1.0f, bx, rc, st);
     }
     prof_end(st, KC_EXP_FWD);
     src = dst;
@@ -2065,18 +2138,15 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, int t, int 
   const HatGeom hg = make_hat(m.rec, m.tz);
   const int* later = !recs && t + 1 < n_sq ? rc + ap.reach_stride : nullptr;
   prof_begin(st, KC_EXP_BWD);
+  const int n = static_cast<int>(m.rec.total / m.rec.ntiles);
   if (first && recs)
-    hipLaunchKernelGGL((k_exp_bwd_hat<true, false>), dim3(hg.total), dim3(ENT), 0, st, ut, gin,
-                       gout, hg, sc, sc, rc, later);
+    launch_hat_r<true, false>(ut, gin, gout, hg, n, sc, rc, later, st);
   else if (first)
-    hipLaunchKernelGGL((k_exp_bwd_hat<true, true>), dim3(hg.total), dim3(ENT), 0, st, ut, gin,
-                       gout, hg, sc, sc, rc, later);
+    launch_hat_r<true, true>(ut, gin, gout, hg, n, sc, rc, later, st);
   else if (recs)
-    hipLaunchKernelGGL((k_exp_bwd_hat<false, false>), dim3(hg.total), dim3(ENT), 0, st, ut, gin,
-                       gout, hg, sc, sc, rc, later);
+    launch_hat_r<false, false>(ut, gin, gout, hg, n, sc, rc, later, st);
   else
-    hipLaunchKernelGGL((k_exp_bwd_hat<false, true>), dim3(hg.total), dim3(ENT), 0, st, ut, gin,
-                       gout, hg, sc, sc, rc, later);
+    launch_hat_r<false, true>(ut, gin, gout, hg, n, sc, rc, later, st);
   prof_end(st, KC_EXP_BWD);
   if (!recs) {
     // (the kernel takes step t > 0 from ckpt + (t - 1) fields)
@@ -2138,6 +2208,7 @@ void run_exp_bwd_recompute(const float* v, const float* g_u, float* g_v, float* 
   const TileGeom tg = make_tiles(g, n);
   const BwdGeom bg = make_bwd(tg, n);
   const MarchGeom m = make_march(tg, n, march_tz(tg, n));
+  const HatGeom hg = make_hat(tg, m.tz);
   const AuxPtrs ap = aux_ptrs(aux, tg, n, n_sq);
   const float scale = ldexpf(1.0f, -n_sq);
   launch_fill_f32(reinterpret_cast<float*>(ap.reach),
@@ -2149,12 +2220,7 @@ void run_exp_bwd_recompute(const float* v, const float* g_u, float* g_v, float* 
     for (int k = 0; k < t; ++k) {
       float* dst = ((t - 1 - k) % 2 == 0) ? rec_a : rec_b;
       prof_begin(st, KC_EXP_FWD);
-      if (k == 0)
-        hipLaunchKernelGGL((k_exp_fwd<true, false>), dim3(m.total), dim3(ENT), 0, st, ut, dst, m,
-                           scale, nullptr, nullptr);
-      else
-        hipLaunchKernelGGL((k_exp_fwd<false, false>), dim3(m.total), dim3(ENT), 0, st, ut, dst, m,
-                           1.0f, nullptr, nullptr);
+      launch_exp_fwd(ut, dst, k == 0, hg, tg, k == 0 ? scale : 1.0f, nullptr, nullptr, st);
       prof_end(st, KC_EXP_FWD);
       ut = dst;
     }

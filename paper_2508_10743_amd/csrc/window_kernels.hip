@@ -491,7 +491,7 @@ struct GaussW {
 constexpr int kGX = 32;
 constexpr int gauss_rows(int R) { return R <= 6 ? 4 : 2; }
 
-template <int R>
+template <int R, bool STREAM>
 __global__ __launch_bounds__(kNT) void k_gauss(const float* __restrict__ in,
                                                float* __restrict__ out, MarchGeom mg, GaussW gw) {
   constexpr int kGR = gauss_rows(R), kGY = kNT * kGR / kGX;
@@ -594,8 +594,8 @@ __global__ __launch_bounds__(kNT) void k_gauss(const float* __restrict__ in,
           float o = 0.0f;
 #pragma unroll
           for (int k = 0; k < W2; ++k) o += gw.w[k] * ring[(j + 1 + k) % W2][r];
-          store_masked(dst, static_cast<uint32_t>((zo * g.d1 + y) * g.d2 + x), o,
-                       zout && y < g.d1);
+          store_masked<STREAM>(dst, static_cast<uint32_t>((zo * g.d1 + y) * g.d2 + x), o,
+                               zout && y < g.d1);
         }
       }
     }
@@ -662,7 +662,10 @@ template <int R>
 void gauss_r(const float* in, float* out, const GaussW& gw, const Geom& g, int nchan,
              hipStream_t st) {
   const MarchGeom mg = make_march(g, nchan, R, kGX, kNT * gauss_rows(R) / kGX);
-  hipLaunchKernelGGL((k_gauss<R>), dim3(mg.total), dim3(kNT), 0, st, in, out, mg, gw);
+  if (static_cast<size_t>(nchan) * g.V * sizeof(float) > kStreamBytes)
+    hipLaunchKernelGGL((k_gauss<R, true>), dim3(mg.total), dim3(kNT), 0, st, in, out, mg, gw);
+  else
+    hipLaunchKernelGGL((k_gauss<R, false>), dim3(mg.total), dim3(kNT), 0, st, in, out, mg, gw);
 }
 
 }  // namespace
