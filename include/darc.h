@@ -164,11 +164,16 @@ int darc_exp_svf_bwd(const float* v, const float* ckpt, const float* g_u, float*
  * the derivative of the trilinear interpolant inside the cell
  * [floor p, floor p + 1] (right-sided at integer positions).
  *   g_u [n][3][V] in/out, accumulated.
+ *
+ * darc_warp3d_grad -- the same with g_u overwritten (g_u [n][3][V] out, must
+ * not alias u).
  * ---------------------------------------------------------------------- */
 int darc_warp3d(const float* img, const float* u, float* out, int n, int d0, int d1, int d2,
                 void* stream);
 int darc_warp3d_bwd(const float* img, const float* u, const float* g_out, float* g_u, int n,
                     int d0, int d1, int d2, void* stream);
+int darc_warp3d_grad(const float* img, const float* u, const float* g_out, float* g_u, int n,
+                     int d0, int d1, int d2, void* stream);
 
 /* ------------------------------------------------------------------------
  * darc_sim_grad -- dissimilarity between each warped subject and the atlas

@@ -115,6 +115,7 @@ PROTOTYPES = {
     "darc_exp_svf_bwd": (c_int, [_P, _P, _P, _P, _I, _I, _I, _I, _I, _P, _Z, _P]),
     "darc_warp3d": (c_int, [_P, _P, _P, _I, _I, _I, _I, _P]),
     "darc_warp3d_bwd": (c_int, [_P, _P, _P, _P, _I, _I, _I, _I, _P]),
+    "darc_warp3d_grad": (c_int, [_P, _P, _P, _P, _I, _I, _I, _I, _P]),
     "darc_sim_grad_ws_bytes": (c_size_t, [_I, _I, _I, _I, _I]),
     "darc_sim_grad": (c_int, [_P, _P, _I, _I, c_float, _P, _P, _I, _I, _I, _I, _P, _Z, _P]),
     "darc_sim_grad_noalloc_max_bytes": (c_size_t, []),

@@ -266,8 +266,18 @@ int darc_warp3d_bwd(const float* img, const float* u, const float* g_out, float*
   DARC_TRY(check_dims("darc_warp3d_bwd", n, d0, d1, d2));
   if (n == 0) return ok();
   if (!img || !u || !g_out || !g_u) return fail(DARC_EINVAL, "darc_warp3d_bwd: NULL pointer");
-  launch_warp_bwd(img, u, g_out, g_u, make_geom(d0, d1, d2), n, as_stream(stream));
+  launch_warp_bwd(img, u, g_out, g_u, true, make_geom(d0, d1, d2), n, as_stream(stream));
   return check_launch("darc_warp3d_bwd");
+}
+
+int darc_warp3d_grad(const float* img, const float* u, const float* g_out, float* g_u, int n,
+                     int d0, int d1, int d2, void* stream) {
+  DARC_TRY(check_dims("darc_warp3d_grad", n, d0, d1, d2));
+  if (n == 0) return ok();
+  if (!img || !u || !g_out || !g_u) return fail(DARC_EINVAL, "darc_warp3d_grad: NULL pointer");
+  if (g_u == u) return fail(DARC_EINVAL, "darc_warp3d_grad: g_u must not alias u");
+  launch_warp_bwd(img, u, g_out, g_u, false, make_geom(d0, d1, d2), n, as_stream(stream));
+  return check_launch("darc_warp3d_grad");
 }
 
 // --------------------------------------------------------- dissimilarities

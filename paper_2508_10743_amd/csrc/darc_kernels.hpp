@@ -62,8 +62,8 @@ void set_barrier_ticks(long long ticks);
 // --- warp -----------------------------------------------------------------
 void launch_warp(const float* img, const float* u, float* out, const Geom& g, int n,
                  hipStream_t st);
-void launch_warp_bwd(const float* img, const float* u, const float* gout, float* gu, const Geom& g,
-                     int n, hipStream_t st);
+void launch_warp_bwd(const float* img, const float* u, const float* gout, float* gu, bool acc,
+                     const Geom& g, int n, hipStream_t st);
 
 // --- dissimilarities and regulariser --------------------------------------
 // MSE (or L1 when l1) on given warped images: loss[i * loss_stride] += D_i;

@@ -137,17 +137,18 @@ def warp3d(img: torch.Tensor, u: torch.Tensor) -> torch.Tensor:
 
 def warp3d_bwd(img: torch.Tensor, u: torch.Tensor, g_out: torch.Tensor,
                g_u: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """g_u += g_out * grad I(x + u); a zero g_u is created when None."""
+    """g_u += g_out * grad I(x + u); without g_u, the gradient alone in a new tensor."""
     n, d0, d1, d2 = _images("img", img)
     _same("u", u.shape, "expected", (n, 3, d0, d1, d2))
     _field("u", u)
     _same("g_out", g_out.shape, "img", img.shape)
     _images("g_out", g_out)
     if g_u is None:
-        g_u = torch.zeros_like(u)
-    else:
-        _same("g_u", g_u.shape, "u", u.shape)
-        _field("g_u", g_u)
+        g_u = torch.empty_like(u)
+        _call("darc_warp3d_grad", _p(img), _p(u), _p(g_out), _p(g_u), n, d0, d1, d2, _stream())
+        return g_u
+    _same("g_u", g_u.shape, "u", u.shape)
+    _field("g_u", g_u)
     _call("darc_warp3d_bwd", _p(img), _p(u), _p(g_out), _p(g_u), n, d0, d1, d2, _stream())
     return g_u
 
