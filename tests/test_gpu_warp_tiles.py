@@ -1,5 +1,6 @@
 """The warp and its adjoint at the edges of their 32 x 4 x 2 tiles, both forms of
-the adjoint (accumulated and overwritten)."""
+the adjoint (accumulated and overwritten), and centring at the edges of the
+register-held subject counts."""
 
 import numpy as np
 import pytest
@@ -31,3 +32,13 @@ def test_warp_and_both_adjoints(dims):
         ref = O.warp3d_bwd(img[i], u[i], gr[i])
         assert np.abs(fresh[i] - ref).max() <= 48 * EPS
         assert np.abs(total[i] - (acc[i] + ref)).max() <= 52 * EPS
+
+
+@pytest.mark.parametrize("n", [1, 8, 9, 16, 17, 24, 25, 32, 33])
+def test_center_counts(n):
+    u = np.random.default_rng(n).uniform(-2.0, 2.0, (n, 3, 3, 5, 7)).astype(np.float32)
+    t = torch.from_numpy(u).cuda()
+    mean = D.center(t).cpu().numpy()
+    ref = u.astype(np.float64).mean(0)
+    assert np.abs(mean - ref).max() <= 2 * EPS * 2.0
+    assert np.abs(t.cpu().numpy() - (u - ref)).max() <= 2 * EPS * 4.0
