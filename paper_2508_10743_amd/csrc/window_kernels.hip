@@ -127,11 +127,10 @@ __global__ __launch_bounds__(kNT) void k_lncc_fwd(const float* __restrict__ wimg
     for (int j = 0; j < W; ++j) ring[j][c] = 0.0;
   }
   double acc = 0.0;
-  // planes walked: the chunk and R on either side, padded to a multiple of W
-  // so that the unrolled body has no branch around its loads and stores
-  // (padding planes stage clamped values and store nothing)
+  // planes walked: the chunk and R on either side; the unrolled body leaves
+  // the loop after the last output instead of branching around its loads and
+  // stores
   const int nplanes = (tl.z1 - tl.z0) + 2 * R;
-  const int npad = (nplanes + W - 1) / W * W;
   // Staged positions of this thread (NPRE per plane): the next plane is
   // loaded into registers while the current one is summed.  Loads are
   // unconditional from clamped positions; out-of-volume values become zeros
@@ -164,28 +163,41 @@ __global__ __launch_bounds__(kNT) void k_lncc_fwd(const float* __restrict__ wimg
 #pragma unroll
     for (int k = 0; k < 4; ++k) fo[k] = masked_out(F + static_cast<size_t>(k) * g.V, g.V);
   }
+  auto stage = [&](int p) {
+    const int zz = tl.z0 - R + p;
+    const bool zin = (zz >= 0) && (zz < g.d0);
+#pragma unroll
+    for (int k = 0; k < NPRE; ++k) {
+      const int e = tid + k * kNT;
+      if (k + 1 < NPRE || e < HY * HX) {
+        const bool in = zin && pin[k];
+        sI[e] = in ? pI[k] : 0.0f;
+        sJ[e] = in ? pJ[k] : 0.0f;
+      }
+    }
+  };
+  // Two phases per plane p, a barrier after each: (A) row sums of plane p,
+  // and the output of plane p - 1 from its column sums; (B) column sums of
+  // plane p, and staging of plane p + 1.  Row sums, column sums and staged
+  // planes are each read in the phase before the one that overwrites them.
+  // The kernel waits more than it computes (three waves per SIMD, half the
+  // vector issue slots used): with a barrier after each of staging, row sums,
+  // column sums and output, statistics and adjoint of 16 x 160 x 192 x 160 took
+  // 1.62 ms, with these two 1.51; 2 x 61 x 75 x 67, window 5: 43.6 and 39.5 us.
   load_plane(0);
-  for (int base = 0; base < npad; base += W) {
+  stage(0);
+  load_plane(1);
+  for (int e = tid; e < 5 * kTY * kTX; e += kNT) (&sc[0][0])[e] = 0.0;  // "plane -1"
+  __syncthreads();
+  for (int base = 0;; base += W) {
 #pragma unroll
     for (int j = 0; j < W; ++j) {
       const int p = base + j;
       {
-        const int zz = tl.z0 - R + p;
-        const bool zin = (zz >= 0) && (zz < g.d0);
-#pragma unroll
-        for (int k = 0; k < NPRE; ++k) {
-          const int e = tid + k * kNT;
-          if (k + 1 < NPRE || e < HY * HX) {
-            const bool in = zin && pin[k];
-            sI[e] = in ? pI[k] : 0.0f;
-            sJ[e] = in ? pJ[k] : 0.0f;
-          }
-        }
-        load_plane(p + 1);
-        __syncthreads();
-        // row sums along x, two neighbouring outputs per thread: the second
-        // slides the first by one (add the entering tap, drop the leaving one)
-        for (int e = tid; e < HY * (kTX / 2); e += kNT) {
+        // (A) row sums along x, two neighbouring outputs per thread: the
+        // second slides the first by one (add the entering tap, drop the
+        // leaving one)
+        for (int e = tid; p < nplanes && e < HY * (kTX / 2); e += kNT) {
           const int hy = e / (kTX / 2), cx = 2 * (e - hy * (kTX / 2));
           // (scalar loads: staging the W + 1 taps in registers would push
           // the kernel past the register budget of three waves per SIMD)
@@ -214,16 +226,14 @@ __global__ __launch_bounds__(kNT) void k_lncc_fwd(const float* __restrict__ wimg
           sr[3][o + 1] = a3 + (jn * jn - jo * jo);
           sr[4][o + 1] = a4 + (in * jn - io * jo);
         }
-        __syncthreads();
-        column_sums<W, 5>(&sr[0][0], &sc[0][0], tid);
-        __syncthreads();
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
+          constexpr int kPrev = W - 1;
           const double P = sc[c][ly * kTX + lx];
-          S[c] += P - ring[j][c];
-          ring[j][c] = P;
+          S[c] += P - ring[(j + kPrev) % W][c];
+          ring[(j + kPrev) % W][c] = P;
         }
-        const int zo = zz - R;
+        const int zo = tl.z0 - 2 * R + p - 1;
         const int y = tl.yb + ly, x = tl.xb + lx;
         const bool out = zo >= tl.z0 && zo < tl.z1 && y < g.d1 && x < g.d2;
         float fv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -249,10 +259,17 @@ __global__ __launch_bounds__(kNT) void k_lncc_fwd(const float* __restrict__ wimg
 #pragma unroll
           for (int k = 0; k < 4; ++k) store_masked(fo[k], idx, fv[k], out);
         }
+        if (p >= nplanes) goto done;
+        __syncthreads();
+        // (B)
+        column_sums<W, 5>(&sr[0][0], &sc[0][0], tid);
+        stage(p + 1);
+        load_plane(p + 2);
         __syncthreads();
       }
     }
   }
+done:
   const double tot = block_sum<kNT>(acc, red);
   if (tid == 0) atomicAdd(loss + static_cast<size_t>(tl.chan) * loss_stride, tot * neg_inv_v);
 }
@@ -336,37 +353,113 @@ __global__ __launch_bounds__(kNT, W <= 9 ? 3 : 2) void k_lncc_bwd(
 #pragma unroll
     for (int c = 0; c < 3; ++c) nu[c] = uf[static_cast<size_t>(c) * g.V + i];
   }
-  for (int base = 0; base < nplanes; base += W) {
+  auto stage = [&]() {
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int e = tid + k * kNT;
+      if (e < HY * HX) {
+        const bool ok = pzin && ein[k];
+        sIn[0][e] = ok ? pre[k][0] : 0.0f;
+        sIn[1][e] = ok ? pre[k][1] : 0.0f;
+        sIn[2][e] = ok ? pre[k][2] : 0.0f;
+        sIn[3][e] = ok ? pre[k][3] : 0.0f;
+      }
+    }
+  };
+  const bool live = tl.yb + ly < g.d1 && tl.xb + lx < g.d2;
+  // Two phases per plane p, a barrier after each, as in the forward kernel:
+  // (A) row sums of plane p and the output of plane p - 1; (B) column sums of
+  // plane p, staging of plane p + 1, and the loads of plane p's output, then
+  // of plane p + 2 (so that waiting for the former does not wait for the
+  // latter).
+  stage();
+  load_plane(1);
+  for (int e = tid; e < 4 * kTY * kTX; e += kNT) (&sc[0][0])[e] = 0.0;  // "plane -1"
+  float eJ = 0.0f, eI = 0.0f;
+  float2 cr[4] = {};  // corner rows (a, b): the pair (jj, jj + 1) along d2
+  float ct[3] = {};
+  unsigned cmask = 0u, chalf = 0u;
+  __syncthreads();
+  for (int base = 0;; base += W) {
 #pragma unroll
     for (int j = 0; j < W; ++j) {
       const int p = base + j;
-      if (p < nplanes) {
-        const int zz = tl.z0 - R + p;
+      {
+        // (A) row sums along x, two neighbouring outputs per thread (sliding)
+        for (int e = tid; p < nplanes && e < HY * (kTX / 2); e += kNT) {
+          const int hy = e / (kTX / 2), cx = 2 * (e - hy * (kTX / 2));
+          const int o = hy * kTX + cx;
 #pragma unroll
-        for (int k = 0; k < NE; ++k) {
-          const int e = tid + k * kNT;
-          if (e < HY * HX) {
-            const bool ok = pzin && ein[k];
-            sIn[0][e] = ok ? pre[k][0] : 0.0f;
-            sIn[1][e] = ok ? pre[k][1] : 0.0f;
-            sIn[2][e] = ok ? pre[k][2] : 0.0f;
-            sIn[3][e] = ok ? pre[k][3] : 0.0f;
+          for (int c = 0; c < 4; ++c) {
+            // aligned 8-byte pairs
+            const float2* pr = reinterpret_cast<const float2*>(&sIn[c][hy * HX + cx]);
+            double t[W + 1];
+#pragma unroll
+            for (int q = 0; q < (W + 1) / 2; ++q) {
+              const float2 a = pr[q];
+              t[2 * q] = a.x;
+              t[2 * q + 1] = a.y;
+            }
+            double a = 0.0;
+#pragma unroll
+            for (int k = 0; k < W; ++k) a += t[k];
+            sr[c][o] = a;
+            sr[c][o + 1] = a + (t[W] - t[0]);
           }
         }
-        // the output voxel's own values, issued before the next plane's
-        // factors so that waiting for them does not wait for those too
-        const int zo = zz - R;
-        const int y = tl.yb + ly, x = tl.xb + lx;
-        const int idx = out_idx(zo);
-        const float eJ = atlas[tl.chan * astr + idx];
-        const float eI = wimg[tl.chan * wstr + idx];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          constexpr int kPrev = W - 1;
+          const double P = sc[c][ly * kTX + lx];
+          S[c] += P - ring[(j + kPrev) % W][c];
+          ring[(j + kPrev) % W][c] = P;
+        }
+        const int zo = tl.z0 - 2 * R + p - 1;
+        if (zo >= tl.z0 && live) {
+          const int idx = out_idx(zo);
+          const size_t vidx = static_cast<size_t>(tl.chan) * g.V + idx;
+          const double Jc = eJ;
+          const double Ic = eI;
+          const double gI = neg_inv_v * (Jc * S[0] - S[1] - Ic * S[2] + S[3]);
+          if (!FUSED) {
+            gw[vidx] = static_cast<float>(gI);
+          } else {
+            const size_t off = static_cast<size_t>(tl.chan) * 3 * g.V;
+            const float* f = uf;
+            float cv[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const float2 pr = cr[k >> 1];
+              const float vk = ((chalf >> (k & 1)) & 1u) ? pr.y : pr.x;
+              cv[k] = ((cmask >> k) & 1u) ? vk : 0.0f;
+            }
+            const Tri t = tri_eval(cv, ct[0], ct[1], ct[2]);
+            float r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
+            if (rw.on) {
+              r0 = reg_at(f, g, idx, zo, oy, ox, rw, racc);
+              r1 = reg_at(f + g.V, g, idx, zo, oy, ox, rw, racc);
+              r2 = reg_at(f + 2 * g.V, g, idx, zo, oy, ox, rw, racc);
+            }
+            const float gf = static_cast<float>(gI);
+            float* o = gu + off;
+            o[idx] = gf * t.d0 + r0;
+            o[g.V + idx] = gf * t.d1 + r1;
+            o[2 * g.V + idx] = gf * t.d2 + r2;
+          }
+        }
+        if (p >= nplanes) goto done;
+        __syncthreads();
+        // (B)
+        column_sums<W, 4>(&sr[0][0], &sc[0][0], tid);
+        stage();
+        const int zn = tl.z0 - 2 * R + p;  // output plane of the next (A)
+        const int idx = out_idx(zn);
+        eJ = atlas[tl.chan * astr + idx];
+        eI = wimg[tl.chan * wstr + idx];
         // fused: the image corners around x + u (zero padding applied when
         // they are used), then u of the next plane's output voxel
-        float2 cr[4];  // corner rows (a, b): the pair (jj, jj + 1) along d2
-        float ct[3];
-        unsigned cmask = 0u, chalf = 0u;
         if (FUSED) {
-          const int zc = min(max(zo, tl.z0), g.d0 - 1);
+          const int zc = min(max(zn, tl.z0), g.d0 - 1);
           int ci[3];
           cell_zero(zc, sane(nu[0]), ci[0], ct[0]);
           cell_zero(oy, sane(nu[1]), ci[1], ct[1]);
@@ -390,6 +483,7 @@ __global__ __launch_bounds__(kNT, W <= 9 ? 3 : 2) void k_lncc_bwd(
             const int j0 = (r >> 1) ? hi[0] : lo[0], j1 = (r & 1) ? hi[1] : lo[1];
             cr[r] = ld_pair(Io + (j0 * g.d1 + j1) * g.d2 + jj);
           }
+          cmask = 0u;
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const int ka = k >> 2, kb = (k >> 1) & 1, kc = k & 1;
@@ -397,78 +491,16 @@ __global__ __launch_bounds__(kNT, W <= 9 ? 3 : 2) void k_lncc_bwd(
                             ((kc ? inh : inl) & 4u);
             cmask |= static_cast<unsigned>(ok) << k;
           }
-          const int in = out_idx(zo + 1);
+          const int in = out_idx(zn + 1);
 #pragma unroll
           for (int c = 0; c < 3; ++c) nu[c] = uf[static_cast<size_t>(c) * g.V + in];
         }
-        load_plane(p + 1);  // past the chunk: clamped, never staged
-        __syncthreads();
-        // row sums along x, two neighbouring outputs per thread (sliding)
-        for (int e = tid; e < HY * (kTX / 2); e += kNT) {
-          const int hy = e / (kTX / 2), cx = 2 * (e - hy * (kTX / 2));
-          const int o = hy * kTX + cx;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            // aligned 8-byte pairs
-            const float2* pr = reinterpret_cast<const float2*>(&sIn[c][hy * HX + cx]);
-            double t[W + 1];
-#pragma unroll
-            for (int q = 0; q < (W + 1) / 2; ++q) {
-              const float2 a = pr[q];
-              t[2 * q] = a.x;
-              t[2 * q + 1] = a.y;
-            }
-            double a = 0.0;
-#pragma unroll
-            for (int k = 0; k < W; ++k) a += t[k];
-            sr[c][o] = a;
-            sr[c][o + 1] = a + (t[W] - t[0]);
-          }
-        }
-        __syncthreads();
-        column_sums<W, 4>(&sr[0][0], &sc[0][0], tid);
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const double P = sc[c][ly * kTX + lx];
-          S[c] += P - ring[j][c];
-          ring[j][c] = P;
-        }
-        if (zo >= tl.z0 && y < g.d1 && x < g.d2) {
-          const size_t vidx = static_cast<size_t>(tl.chan) * g.V + idx;
-          const double Jc = eJ;
-          const double Ic = eI;
-          const double gI = neg_inv_v * (Jc * S[0] - S[1] - Ic * S[2] + S[3]);
-          if (!FUSED) {
-            gw[vidx] = static_cast<float>(gI);
-          } else {
-            const size_t off = static_cast<size_t>(tl.chan) * 3 * g.V;
-            const float* f = uf;
-            float cv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const float2 pr = cr[k >> 1];
-              const float vk = ((chalf >> (k & 1)) & 1u) ? pr.y : pr.x;
-              cv[k] = ((cmask >> k) & 1u) ? vk : 0.0f;
-            }
-            const Tri t = tri_eval(cv, ct[0], ct[1], ct[2]);
-            float r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
-            if (rw.on) {
-              r0 = reg_at(f, g, idx, zo, y, x, rw, racc);
-              r1 = reg_at(f + g.V, g, idx, zo, y, x, rw, racc);
-              r2 = reg_at(f + 2 * g.V, g, idx, zo, y, x, rw, racc);
-            }
-            const float gf = static_cast<float>(gI);
-            float* o = gu + off;
-            o[idx] = gf * t.d0 + r0;
-            o[g.V + idx] = gf * t.d1 + r1;
-            o[2 * g.V + idx] = gf * t.d2 + r2;
-          }
-        }
+        load_plane(p + 2);  // past the chunk: clamped, never used
         __syncthreads();
       }
     }
   }
+done:
   if (FUSED && rw.on) {
     const double tot = block_sum<kNT>(racc, red);
     if (tid == 0) atomicAdd(loss + static_cast<size_t>(tl.chan) * loss_stride, rw.lam * tot);
@@ -513,10 +545,11 @@ __global__ __launch_bounds__(kNT) void k_gauss(const float* __restrict__ in,
   for (int j = 0; j < W2; ++j)
 #pragma unroll
     for (int r = 0; r < kGR; ++r) ring[j][r] = 0.0f;
-  // planes walked: the chunk and R on either side, padded to a multiple of
-  // W2 so that the unrolled body has no branch around its loads and stores
+  // planes walked: the chunk and R on either side; the unrolled body leaves
+  // the loop after the last instead of branching around its loads and stores
+  // (padding the walk to a multiple of W2 cost a tenth: 16 x 160 x 192 x 224,
+  // sigma 1.5, 0.735 against 0.69 ms)
   const int nplanes = (tl.z1 - tl.z0) + 2 * R;
-  const int npad = (nplanes + W2 - 1) / W2 * W2;
   // staged positions: volume offset (replicated border; positions past the
   // staged plane load a clamped voxel that is never staged) and LDS slot
   int eoff[NE], eslot[NE];
@@ -541,10 +574,11 @@ __global__ __launch_bounds__(kNT) void k_gauss(const float* __restrict__ in,
   };
   load_plane(0);
   const int x = tl.xb + lx;
-  for (int base = 0; base < npad; base += W2) {
+  for (int base = 0;; base += W2) {
 #pragma unroll
     for (int j = 0; j < W2; ++j) {
       const int p = base + j;
+      if (p >= nplanes) return;
       {
 #pragma unroll
         for (int k = 0; k < NE; ++k)
