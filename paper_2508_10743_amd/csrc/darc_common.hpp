@@ -302,6 +302,13 @@ __device__ __forceinline__ float load_masked(const MaskedIn& m, uint32_t byte_of
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(m.r, byte_offset, 0, 0));
 }
 
+// (the wave-uniform part of the offset is added outside the range check)
+__device__ __forceinline__ uint4 load_masked16(const MaskedIn& m, uint32_t byte_offset,
+                                               uint32_t uniform_offset) {
+  return __builtin_bit_cast(
+      uint4, __builtin_amdgcn_raw_buffer_load_b128(m.r, byte_offset, uniform_offset, 0));
+}
+
 // The 8 corners of one field component at a border cell (always in range).
 __device__ __forceinline__ void corners_border(const float* __restrict__ f, const Geom& g,
                                                int base, float (&c)[8]) {

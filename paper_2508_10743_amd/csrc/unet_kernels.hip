@@ -244,16 +244,24 @@ struct LdsBrick {
   static constexpr int NVOX = (LBZ + 2) * NY * NX;
 };
 
-template <int NT16, int MT, int X0, int CG>
-__global__ __launch_bounds__(CNT) void k_conv3d_lds(const uint16_t* __restrict__ x0,
-                                                    const uint16_t* __restrict__ x1,
-                                                    const uint16_t* __restrict__ w,
-                                                    const float* __restrict__ bias,
-                                                    uint16_t* __restrict__ y16,
-                                                    float* __restrict__ y32, ConvGeom cg,
-                                                    int nbz, int nby, int nbx) {
+// ROWS (16 or 32 output channels, chunks of 16 input channels): a K step holds
+// two of the nine (d0, d2) taps, and its A fragment of input row y + b serves
+// the three d1 taps b of three row tiles: MT + 2 LDS reads for 3 MT products
+// instead of one each.  A chunk's weight fragments are staged in LDS beside it
+// (every wave read them all from the cache otherwise, 16 rows of kpad per
+// instruction, and the loop waited for that).  Bound by LDS reads and the
+// matrix pipes together: 13 reads of 8 cycles for 24 products of 4 (per CU) at
+// 16 channels and MT = 8, of which three blocks fit a CU.  48 -> 16 channels
+// at 4 x 96 x 112 x 96: 292 us without row reuse, 228 with MT = 4, 195
+// with MT = 8; the network's forward pass 1.07 -> 0.83 ms.
+template <int NT16, int MT, int X0, int CG, bool ROWS>
+__global__ __launch_bounds__(CNT, ROWS ? (MT == 8 ? 4 : 5) - NT16 : 1) void k_conv3d_lds(
+    const uint16_t* __restrict__ x0, const uint16_t* __restrict__ x1,
+    const uint16_t* __restrict__ w, const float* __restrict__ bias, uint16_t* __restrict__ y16,
+    float* __restrict__ y32, ConvGeom cg, int nbz, int nby, int nbx) {
   using B = LdsBrick<MT>;
-  constexpr int SU = CG % 2 ? CG : CG + 1;  // voxel stride in 16-byte units (odd)
+  // voxel stride in 16-byte units: odd, or (ROWS) without padding
+  constexpr int SU = ROWS || CG % 2 ? CG : CG + 1;
   constexpr int NPAIR = 27 * CG;
   constexpr int NSTEP = (NPAIR + 3) / 4;
   constexpr int NUNIT = B::NVOX * CG;          // 16-byte units staged per chunk
@@ -261,7 +269,11 @@ __global__ __launch_bounds__(CNT) void k_conv3d_lds(const uint16_t* __restrict__
   static_assert(CNT % CG == 0, "a thread's staging units share one channel group");
   static_assert(NU <= 16, "staging flags fit one word");
   __shared__ uint4 brick[B::NVOX * SU];
-  __shared__ int2 ktab[NSTEP * 4];  // (A byte offset at row tile 0, weight offset) per pair
+  // (A byte offset at row tile 0, weight offset) per pair
+  __shared__ int2 ktab[ROWS ? 1 : NSTEP * 4];
+  // ROWS: the chunk's weight fragments, [K step][d1 tap][column tile][lane]
+  constexpr int NWF = 15 * NT16, NWU = (NWF * 64 + CNT - 1) / CNT;
+  __shared__ uint4 wfrag[ROWS ? NWF * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kg = lane >> 4;
   // block -> (subject, brick); consecutive bricks of a subject share an XCD
@@ -285,7 +297,7 @@ __global__ __launch_bounds__(CNT) void k_conv3d_lds(const uint16_t* __restrict__
   const int nco0 = blockIdx.y * 16 * NT16;
 
   // the K-step table: pair q = 4 st + lane group, tap q / CG, group q % CG
-  if (threadIdx.x < NSTEP * 4) {
+  if (!ROWS && threadIdx.x < NSTEP * 4) {
     const int q = threadIdx.x;
     const int tap = q < NPAIR ? q / CG : 0, g = q % CG;
     const int toff = ((tap / 9) * B::NY + (tap / 3) % 3) * B::NX + tap % 3;
@@ -348,6 +360,122 @@ __global__ __launch_bounds__(CNT) void k_conv3d_lds(const uint16_t* __restrict__
         pre[j] = *reinterpret_cast<const uint4*>(src);
     }
   };
+  if constexpr (ROWS) {
+    static_assert(CG == 2 && X0 != 2, "two channel groups per chunk");
+    // staging through range-checked loads (units outside the volume read zeros
+    // without an access); the channel of a chunk is the uniform offset
+    const MaskedIn b0 = masked_in(reinterpret_cast<const float*>(sx0),
+                                  static_cast<uint32_t>(vin0 * cg.c0 / 2));
+    const MaskedIn b1 = masked_in(reinterpret_cast<const float*>(x1 ? sx1 + cg.c0 : sx0),
+                                  static_cast<uint32_t>((x1 ? vin1 * cg.c1 : vin0 * cg.c0) / 2));
+    const MaskedIn bw = masked_in(reinterpret_cast<const float*>(w),
+                                  static_cast<uint32_t>(static_cast<long long>(cg.cout) * cg.kpad / 2));
+    uint32_t uo0[NU], uo1[NU];  // byte offsets in x0 and x1
+    {
+      int ex = (threadIdx.x / CG) % B::NX, ey = (threadIdx.x / CG) / B::NX % B::NY,
+          ez = (threadIdx.x / CG) / (B::NX * B::NY);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int p0 = oz - 1 + ez, p1 = oy - 1 + ey, p2 = ox - 1 + ex;
+        const bool in = threadIdx.x + u * CNT < NUNIT &&
+                        static_cast<unsigned>(p0) < static_cast<unsigned>(cg.i0) &&
+                        static_cast<unsigned>(p1) < static_cast<unsigned>(cg.i1) &&
+                        static_cast<unsigned>(p2) < static_cast<unsigned>(cg.i2);
+        const uint32_t vf = static_cast<uint32_t>((p0 * cg.i1 + p1) * cg.i2 + p2);
+        const uint32_t vh = half ? static_cast<uint32_t>(((p0 >> 1) * h1 + (p1 >> 1)) * h2 + (p2 >> 1))
+                                 : vf;
+        uo0[u] = in ? (vh * cg.c0 + sg * 8) * 2u : kNoAccess;
+        uo1[u] = in ? (vf * cg.c1 + sg * 8) * 2u : kNoAccess;
+        // the next unit is CNT / CG voxels on
+        constexpr int kStep = CNT / CG, kSx = kStep % B::NX, kSy = kStep / B::NX % B::NY,
+                      kSz = kStep / (B::NX * B::NY);
+        ex += kSx;
+        ey += kSy;
+        ez += kSz;
+        if (ex >= B::NX) {
+          ex -= B::NX;
+          ++ey;
+        }
+        if (ey >= B::NY) {
+          ey -= B::NY;
+          ++ez;
+        }
+      }
+    }
+    auto load_rows = [&](int cb) {
+      const int ch = cb * 8;
+      if (ch < cg.c0) {  // whole chunks: c0 is a multiple of 16 where there is an x1
+#pragma unroll
+        for (int u = 0; u < NU; ++u) pre[u] = load_masked16(b0, uo0[u], ch * 2u);
+      } else {
+        // past the last chunk: the last again, never staged
+        const uint32_t c = static_cast<uint32_t>(min(ch, cg.c0 + cg.c1 - 16) - cg.c0) * 2u;
+        const bool one = cg.c1 > 0;
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          pre[u] = load_masked16(one ? b1 : b0, one ? uo1[u] : kNoAccess, one ? c : 0u);
+      }
+    };
+    // per K step: the lane's A offset (row 0)
+    uint32_t ao[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const int m = min(2 * k + (kg >> 1), 8);
+      ao[k] = static_cast<uint32_t>((m / 3 * B::NY * B::NX + m % 3) * SU * 16 + (kg & 1) * 16);
+    }
+    // weight fragments staged by this thread: u * CWAVES + wave, its own lane's
+    uint32_t wo[NWU];
+#pragma unroll
+    for (int u = 0; u < NWU; ++u) {
+      const int f = u * CWAVES + wave;
+      const int k = f / (3 * NT16), b3 = f / NT16 % 3, t = f % NT16;
+      const int m = 2 * k + (kg >> 1), co = nco0 + t * 16 + r;
+      wo[u] = f < NWF && m < 9 && co < cg.cout
+                  ? (static_cast<uint32_t>(co) * cg.kpad +
+                     ((m / 3 * 9 + b3 * 3 + m % 3) * cvec + (kg & 1)) * 8) * 2u
+                  : kNoAccess;
+    }
+    uint4 wpre[NWU];
+    auto load_weights = [&](int cb) {
+#pragma unroll
+      for (int u = 0; u < NWU; ++u)
+        wpre[u] = load_masked16(bw, wo[u], static_cast<uint32_t>(min(cb, cvec - CG)) * 16u);
+    };
+    load_rows(0);
+    load_weights(0);
+    for (int cb = 0; cb < cvec; cb += CG) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (u < NU - 1 || !lastu) brick[slot0 + u * SLOTJ] = pre[u];
+      }
+#pragma unroll
+      for (int u = 0; u < NWU; ++u)
+        if (u * CWAVES + wave < NWF) wfrag[(u * CWAVES + wave) * 64 + lane] = wpre[u];
+      __syncthreads();
+      load_rows(cb + CG);
+      load_weights(cb + CG);
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        uint4 a[MT + 2];
+#pragma unroll
+        for (int y = 0; y < MT + 2; ++y)
+          a[y] = *reinterpret_cast<const uint4*>(abase + ao[k] + y * B::NX * SU * 16);
+#pragma unroll
+        for (int b3 = 0; b3 < 3; ++b3) {
+#pragma unroll
+          for (int t = 0; t < NT16; ++t) {
+            const uint4 bf = wfrag[((k * 3 + b3) * NT16 + t) * 64 + lane];
+#pragma unroll
+            for (int q2 = 0; q2 < MT; ++q2)
+              acc[q2][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, a[q2 + b3]), __builtin_bit_cast(bf16x8, bf),
+                  acc[q2][t], 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();
+    }
+  } else {
   load_chunk(0);
   for (int cb = 0; cb < cvec; cb += CG) {
     // stage channel groups cb .. cb + CG - 1 of the input brick, then load
@@ -381,6 +509,7 @@ __global__ __launch_bounds__(CNT) void k_conv3d_lds(const uint16_t* __restrict__
       }
     }
     __syncthreads();
+  }
   }
   // epilogue: lane holds d2 offsets 4 kg .. 4 kg + 3 of channel column r
   const int z = oz + wave;
@@ -1349,13 +1478,34 @@ void conv3d_lds_x0(int mode, dim3 grid, const uint16_t* x0, const uint16_t* x1, 
                    const float* bias, uint16_t* y16, float* y32, const ConvGeom& cg, int nbz,
                    int nby, int nbx, hipStream_t st) {
   if (mode == 0)
-    hipLaunchKernelGGL((k_conv3d_lds<NT16, kLdsMT, 0, CG>), grid, dim3(CNT), 0, st, x0, x1, w,
-                       bias, y16, y32, cg, nbz, nby, nbx);
+    hipLaunchKernelGGL((k_conv3d_lds<NT16, kLdsMT, 0, CG, false>), grid, dim3(CNT), 0, st, x0, x1,
+                       w, bias, y16, y32, cg, nbz, nby, nbx);
   else if (mode == 1)
-    hipLaunchKernelGGL((k_conv3d_lds<NT16, kLdsMT, 1, CG>), grid, dim3(CNT), 0, st, x0, x1, w,
+    hipLaunchKernelGGL((k_conv3d_lds<NT16, kLdsMT, 1, CG, false>), grid, dim3(CNT), 0, st, x0, x1,
+                       w, bias, y16, y32, cg, nbz, nby, nbx);
+  else
+    hipLaunchKernelGGL((k_conv3d_lds<NT16, kLdsMT, 2, CG, false>), grid, dim3(CNT), 0, st, x0, x1,
+                       w, bias, y16, y32, cg, nbz, nby, nbx);
+}
+
+// Row reuse needs chunks of 16 channels from one tensor and 31-bit byte offsets
+// within a subject.
+bool conv_rows(int mode, const ConvGeom& cg) {
+  const long long v = static_cast<long long>(cg.i0) * cg.i1 * cg.i2;
+  return mode != 2 && (cg.c0 + cg.c1) % 16 == 0 && (cg.c1 == 0 || cg.c0 % 16 == 0) &&
+         v * 2 * cg.c0 < (1ll << 31) && v * 2 * cg.c1 < (1ll << 31) &&
+         2ll * cg.cout * cg.kpad < (1ll << 31);
+}
+
+template <int NT16, int MT>
+void conv3d_rows(int mode, dim3 grid, const uint16_t* x0, const uint16_t* x1, const uint16_t* w,
+                 const float* bias, uint16_t* y16, float* y32, const ConvGeom& cg, int nbz, int nby,
+                 int nbx, hipStream_t st) {
+  if (mode == 0)
+    hipLaunchKernelGGL((k_conv3d_lds<NT16, MT, 0, 2, true>), grid, dim3(CNT), 0, st, x0, x1, w,
                        bias, y16, y32, cg, nbz, nby, nbx);
   else
-    hipLaunchKernelGGL((k_conv3d_lds<NT16, kLdsMT, 2, CG>), grid, dim3(CNT), 0, st, x0, x1, w,
+    hipLaunchKernelGGL((k_conv3d_lds<NT16, MT, 1, 2, true>), grid, dim3(CNT), 0, st, x0, x1, w,
                        bias, y16, y32, cg, nbz, nby, nbx);
 }
 
@@ -1410,10 +1560,31 @@ void launch_conv3d(const uint16_t* x0, const uint16_t* x1, const uint16_t* w, co
     const int nbx = (cg.o2 + LBX - 1) / LBX;
     const long long per = static_cast<long long>(cg.o0) * cg.o1 * cg.o2;
     const uint32_t gx = static_cast<uint32_t>(static_cast<long long>(nbz) * nby * nbx * (cg.nvox / per));
-    // column tiles per wave: 48 channels where they divide cout and 64 do
-    // not (the input gradients of concatenated layers: 48, 96), so that no
-    // tile is computed for channels past cout
-    if (cg.cout <= 16)
+    if (conv_rows(mode, cg)) {
+      // column blocks of 16 or 32 channels: the weights of wider ones leave
+      // room for one or two blocks per CU (192 -> 64 at 4 x 24 x 28 x 24: 65 us
+      // in blocks of 32, 74 of 16, 131 of 64; the adjoint of 96 -> 32 at 4 x 48
+      // x 56 x 48 with its weight gradient in 353 us, 379 and, of 48, 398).
+      // Bricks of 8 rows where they compute no more rows than those of 4 (64 ->
+      // 32 at 4 x 48 x 56 x 48: 80 us, of 4 92; 192 -> 64 with 28 rows: 73, of
+      // 4 65), except for FP32 outputs, whose stores want the blocks in flight
+      // (that adjoint: 400 us, of 4 353)
+      const uint32_t gy = static_cast<uint32_t>(cg.cout <= 16 ? 1 : (cg.cout + 31) / 32);
+      if (y16 && (cg.o1 + 7) / 8 * 8 <= nby * kLdsMT) {
+        const int nby8 = (cg.o1 + 7) / 8;
+        const uint32_t gx8 = gx / nby * nby8;
+        if (cg.cout <= 16)
+          conv3d_rows<1, 8>(mode, dim3(gx8, gy), x0, x1, w, bias, y16, y32, cg, nbz, nby8, nbx, st);
+        else
+          conv3d_rows<2, 8>(mode, dim3(gx8, gy), x0, x1, w, bias, y16, y32, cg, nbz, nby8, nbx, st);
+      } else if (cg.cout <= 16) {
+        conv3d_rows<1, kLdsMT>(mode, dim3(gx, gy), x0, x1, w, bias, y16, y32, cg, nbz, nby, nbx, st);
+      } else {
+        conv3d_rows<2, kLdsMT>(mode, dim3(gx, gy), x0, x1, w, bias, y16, y32, cg, nbz, nby, nbx, st);
+      }
+    } else if (cg.cout <= 16)
+      // column tiles per wave: 48 channels where they divide cout and 64 do
+      // not, so that no tile is computed for channels past cout
       conv3d_lds_cg<1>(mode, dim3(gx, 1), x0, x1, w, bias, y16, y32, cg, nbz, nby, nbx, st);
     else if (cg.cout <= 32)
       conv3d_lds_cg<2>(mode, dim3(gx, 1), x0, x1, w, bias, y16, y32, cg, nbz, nby, nbx, st);
