@@ -1128,19 +1128,25 @@ __global__ __launch_bounds__(64) void k_conv_wgrad(int wch, const uint16_t* __re
   }
 }
 
-// Weight gradients of a stride-1, 27-tap layer, all taps of one input
-// channel group at once: a wave takes a co tile of 16, one group of 8 input
-// channels and a run of K steps, a K step being 32 output voxels, R rows
-// (d1) of W = 32 / R along d2.  The input positions that the 27 taps read
-// for them (3 x (R + 2) rows of W + 2 positions, 8 channels each) are staged
-// in LDS once per step; each of the 14 column tiles (taps 2t and 2t + 1,
-// 8 channels each) then reads its B fragment there through the transposing
-// LDS read, lane j of a 16-lane group pointing at the 4 channels 4 (j % 4)..
-// of tile column group j % 4 at voxel base + j / 4.  A step stages 9.6
-// (R = 1), 6.8 (R = 2) or 5.6 (R = 4) input positions per output voxel
-// where the tap-by-tap kernel above loads 27.
-template <int X0, int R>
-__global__ __launch_bounds__(64) void k_conv_wgrad_rows(int wsteps,
+// Weight gradients of a stride-1, 27-tap layer, all taps of an input channel
+// group at once: a block takes a co tile of 16, G groups of 8 input channels
+// (a wave each) and a run of K steps, a K step being 32 output voxels, R rows
+// (d1) of W = 32 / R along d2.  The input positions that the 27 taps read for
+// them (3 x (R + 2) rows of W + 2 positions) are staged in LDS once per step,
+// 16 G contiguous bytes each, and dz once for all waves; each of the 14 column
+// tiles (taps 2t and 2t + 1, 8 channels each) then reads its B fragment there
+// through the transposing LDS read, lane j of a 16-lane group pointing at the
+// 4 channels 4 (j % 4).. of tile column group j % 4 at voxel base + j / 4.  A
+// step stages 9.6 (R = 1) or 5.6 (R = 4) input positions per output voxel
+// where the tap-by-tap kernel above loads 27.  Two buffers, one barrier per
+// step.  Bound by the LDS reads (28 for 14 products, about half of the time)
+// and their latency at three waves per SIMD; 32 channels of dz per wave, half
+// the reads per product, leave two, in the same time.  With 16-byte loads of
+// a group per wave, addressed anew each step, half of the instructions were
+// address arithmetic: 96 -> 32 channels at 4 x 48 x 56 x 48 240 us, now
+// 195; the network's training step 3.19 -> 2.97 ms.
+template <int X0, int R, int G>
+__global__ __launch_bounds__(64 * G) void k_conv_wgrad_rows(int wsteps,
                                                         const uint16_t* __restrict__ dz, int cz,
                                                         const uint16_t* __restrict__ x0,
                                                         const uint16_t* __restrict__ x1,
@@ -1152,17 +1158,19 @@ __global__ __launch_bounds__(64) void k_conv_wgrad_rows(int wsteps,
   constexpr int NPOS = 3 * NYP * NXP;
   constexpr int NLD = (NPOS + 63) / 64;  // staged positions per lane
   constexpr int NTT = 14;                // column tiles: 27 taps (and one empty) x 8 channels
-  __shared__ __align__(16) uint16_t xs[NPOS * 8];  // [position][8 channels]
-  __shared__ __align__(16) uint16_t at[32 * 16];   // dz: [voxel][co]
-  const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
-  const int vl = lane & 31, h = lane >> 5;  // staged voxel of dz, channel half
+  // positions per channel group in LDS: 2 mod 16, so that the staging writes of
+  // a position's groups fall in different banks
+  constexpr int XP = NLD * 64 + 2;
+  __shared__ __align__(16) uint16_t xs[2][G * XP * 8];  // [group][position][8 channels]
+  __shared__ __align__(16) uint16_t at[2][32 * 16];     // dz: [voxel][co]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   // The waves of one run of K steps (every channel group and co tile) are
   // consecutive on one XCD, so that its dz and input rows are read there
   // from L2 after the first of them.
   const int cin = cg.c0 + cg.c1;
   const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x);
-  const int ngrp = cin / 8;
-  const int grp = static_cast<int>(wid % ngrp);  // input channels 8 grp .. 8 grp + 7
+  const int ngrp = cin / (8 * G);
+  const int grp = static_cast<int>(wid % ngrp) * G;  // input channels 8 grp .. 8 (grp + G) - 1
   const uint32_t wrest = wid / ngrp;
   const int ntz = (cg.cout + 15) / 16;
   const int co0 = static_cast<int>(wrest % ntz) * 16;
@@ -1193,125 +1201,150 @@ __global__ __launch_bounds__(64) void k_conv_wgrad_rows(int wsteps,
 #pragma unroll
   for (int t = 0; t < NTT; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   const bool bias = db != nullptr && grp == 0;
-  float bacc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  float bacc[8] = {};
   const long long s0 = static_cast<long long>(chunk) * wsteps;
   const long long s1 = min(s0 + wsteps, nsteps);
-  // The loads of one K step (every load issued, from dz or the subject's
-  // first input voxel where the value is zero; the padding is applied when
-  // staged).  A step's loads are issued before the previous step's
-  // products; past the run the last step is loaded again and never staged.
-  // The step's rows (subject sj, output plane oz, first row oy) and segment
-  // are kept as counters (wave-uniform, advanced once per step: no division
-  // in the loop), and the per-lane offsets are 32-bit (the launch checks
-  // that every input tensor's subject holds fewer than 2^31 elements).
+  // The loads of one K step are issued before the previous step's products;
+  // past the run the last step is loaded again and never staged.  They are
+  // range checked, from the step's first position: a lane's offsets are the
+  // same in every step of a row group, and the padding is a masked offset,
+  // along d2 computed for the first and last step of a row only.  The
+  // step's rows (subject sj, output plane oz, first row oy) and segment are
+  // kept as counters (wave-uniform, advanced once per step: no division in
+  // the loop).
   const long long rg0 = s0 / nseg;  // row group of the first step
   int seg = static_cast<int>(s0 - rg0 * nseg);
   int oy = static_cast<int>(rg0 % nrg) * R;
   int oz = static_cast<int>((rg0 / nrg) % cg.o0);
   int sj = static_cast<int>(rg0 / nrg / cg.o0);
+  // this thread's 16-byte units: of dz (the first wave), channels 8 h .. of
+  // voxel dvox; of the input, group sg of positions sp + 64 q
+  const int dvox = lane >> 1, h = lane & 1;
+  const int sg = threadIdx.x % G, sp = threadIdx.x / G;
+  const uint32_t doff =
+      wave == 0 && co0 + 8 * h < cz
+          ? static_cast<uint32_t>(((dvox / W) * cg.o2 + dvox % W) * cz + co0 + 8 * h) * 2u
+          : kNoAccess;
+  uint32_t xoff[NLD];
+  const int hp = hi1 * hi2;
+#pragma unroll
+  for (int q = 0; q < NLD; ++q) {
+    const int i = sp + 64 * q, pa = i / (NYP * NXP), pb = i / NXP % NYP, xi = i % NXP;
+    const int e = half ? (xi + 1) >> 1 : pa * hp + pb * hi2 + xi;
+    xoff[q] = i < NPOS ? static_cast<uint32_t>(e * cstr + sg * 8) * 2u : kNoAccess;
+  }
+  // of the step's row group: the offsets with its padding, and the tensors at
+  // its first position (one before the row's first along d2 for the input)
+  uint32_t drow, xrow[NLD];
+  const uint16_t *dbase, *xbase;
+  auto start_row = [&]() {
+    const int qz = oz - 1, qy = oy - 1;
+    const int sz = half ? qz >> 1 : qz, sy = half ? qy >> 1 : qy;
+    dbase = dz + ((static_cast<long long>(sj) * cg.o0 + oz) * cg.o1 + oy) * cg.o2 * cz;
+    xbase = src + (static_cast<long long>(sj) * vin + (static_cast<long long>(sz) * hi1 + sy) * hi2 - 1) * cstr + coff;
+    drow = oy + dvox / W < cg.o1 ? doff : kNoAccess;
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) {
+      const int i = sp + 64 * q, pa = i / (NYP * NXP), pb = i / NXP % NYP;
+      const bool in = static_cast<unsigned>(qz + pa) < static_cast<unsigned>(cg.i0) &&
+                      static_cast<unsigned>(qy + pb) < static_cast<unsigned>(cg.i1);
+      uint32_t o = xoff[q];
+      if (half)
+        o += static_cast<uint32_t>((((pa + (qz & 1)) >> 1) * hp + ((pb + (qy & 1)) >> 1) * hi2) * cstr) * 2u;
+      xrow[q] = in ? o : kNoAccess;
+    }
+  };
   auto advance = [&]() {
-    if (++seg == nseg) {
-      seg = 0;
-      oy += R;
-      if (oy >= cg.o1) {
-        oy = 0;
-        if (++oz == cg.o0) {
-          oz = 0;
-          ++sj;
+    if (++seg < nseg) return;
+    seg = 0;
+    oy += R;
+    if (oy >= cg.o1) {
+      oy = 0;
+      if (++oz == cg.o0) {
+        oz = 0;
+        ++sj;
+      }
+    }
+    start_row();
+  };
+  uint4 ca, cx[NLD];
+  auto issue = [&]() {
+    const int xv = seg * W;
+    const MaskedIn md = masked_in(reinterpret_cast<const float*>(dbase + static_cast<long long>(xv) * cz),
+                                  kNoAccess / 4);
+    const MaskedIn mx = masked_in(
+        reinterpret_cast<const float*>(xbase + static_cast<long long>(half ? xv / 2 : xv) * cstr),
+        kNoAccess / 4);
+    uint32_t d = drow, x[NLD];
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) x[q] = xrow[q];
+    if (seg == 0 || xv + W >= cg.o2) {
+      d = xv + dvox % W < cg.o2 ? d : kNoAccess;
+#pragma unroll
+      for (int q = 0; q < NLD; ++q)
+        x[q] = static_cast<unsigned>(xv - 1 + (sp + 64 * q) % NXP) < static_cast<unsigned>(cg.i2)
+                   ? x[q]
+                   : kNoAccess;
+    }
+    ca = load_masked16(md, d, 0u);
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) cx[q] = load_masked16(mx, x[q], 0u);
+  };
+  if (s0 < s1) start_row();
+  if (s0 < s1) issue();
+  int buf = 0;
+  for (long long step = s0; step < s1; ++step, buf ^= 1) {
+    // stage dz of the segment's 32 voxels (zero past the row end) and the
+    // input positions every tap reads (zero padding outside the volume)
+    if (wave == 0) {
+      *reinterpret_cast<uint4*>(&at[buf][dvox * 16 + 8 * h]) = ca;
+      if (bias) {
+        const uint32_t aw[4] = {ca.x, ca.y, ca.z, ca.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          bacc[2 * j] += __uint_as_float(aw[j] << 16);
+          bacc[2 * j + 1] += __uint_as_float(aw[j] & 0xFFFF0000u);
         }
       }
     }
-  };
-  const int vy = vl / W, vx = vl % W;  // the dz voxel this lane stages
-  auto issue = [&](uint4& a, bool& aok, uint4 (&xv)[NLD], bool (&xin)[NLD]) {
-    const int x0v = seg * W;
-    aok = oy + vy < cg.o1 && x0v + vx < cg.o2 && co0 + 8 * h < cz;
-    const uint16_t* dplane = dz + (static_cast<long long>(sj) * cg.o0 + oz) * cg.o1 * cg.o2 * cz;
-    a = *reinterpret_cast<const uint4*>(
-        dplane + (aok ? ((oy + vy) * cg.o2 + x0v + vx) * cz + co0 + 8 * h : 0));
-    const int qz = oz - 1, qy = oy - 1, qx = x0v - 1;
-    const uint16_t* base = src + static_cast<long long>(sj) * vin * cstr + coff;
 #pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int i = lane + 64 * k;
-      const int pa = i / (NYP * NXP), pb = (i / NXP) % NYP, xi = i % NXP;
-      const int pz = qz + pa, py = qy + pb, px = qx + xi;
-      xin[k] = i < NPOS && static_cast<unsigned>(pz) < static_cast<unsigned>(cg.i0) &&
-               static_cast<unsigned>(py) < static_cast<unsigned>(cg.i1) &&
-               static_cast<unsigned>(px) < static_cast<unsigned>(cg.i2);
-      const int pv = half ? ((pz >> 1) * hi1 + (py >> 1)) * hi2 + (px >> 1) : (pz * hi1 + py) * hi2 + px;
-      xv[k] = *reinterpret_cast<const uint4*>(base + static_cast<uint32_t>(xin[k] ? pv * cstr : 0));
-    }
-  };
-  auto keep = [](uint4 q, bool kp) {
-    return make_uint4(kp ? q.x : 0u, kp ? q.y : 0u, kp ? q.z : 0u, kp ? q.w : 0u);
-  };
-  uint4 ca, na, cx[NLD], nx[NLD];
-  bool caok, naok, cxin[NLD], nxin[NLD];
-  if (s0 < s1) issue(ca, caok, cx, cxin);
-  for (long long step = s0; step < s1; ++step) {
-    // stage dz of the segment's 32 voxels (zero past the row end) and the
-    // input positions every tap reads (zero padding outside the volume)
-    ca = keep(ca, caok);
-    *reinterpret_cast<uint4*>(&at[vl * 16 + 8 * h]) = ca;
-    if (bias) {
-      const uint32_t aw[4] = {ca.x, ca.y, ca.z, ca.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        bacc[2 * j] += __uint_as_float(aw[j] << 16);
-        bacc[2 * j + 1] += __uint_as_float(aw[j] & 0xFFFF0000u);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int i = lane + 64 * k;
-      if (i < NPOS) *reinterpret_cast<uint4*>(&xs[i * 8]) = keep(cx[k], cxin[k]);
-    }
+    for (int q = 0; q < NLD; ++q)
+      *reinterpret_cast<uint4*>(&xs[buf][(sg * XP + sp + 64 * q) * 8]) = cx[q];
     if (step + 1 < s1) advance();
-    issue(na, naok, nx, nxin);
-    // one wave: its LDS operations complete in order
-    const bf16x8 afrag = tr_frag(at, g, r);
+    issue();
+    // one barrier per step: the buffer written next was last read before it
+    __syncthreads();
+    const bf16x8 afrag = tr_frag(at[buf], g, r);
     typedef __attribute__((address_space(3))) v4i16* lds_v4;
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
-      const uint16_t* p = xs + vrow + toff[t];
+      const uint16_t* p = xs[buf] + wave * (XP * 8) + vrow + toff[t];
       const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(p));
       const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(p + 4 * 8));
       const bf16x8 bfrag =
           __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afrag, bfrag, acc[t], 0, 0, 0);
     }
-    ca = na;
-    caok = naok;
-#pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-      cx[q] = nx[q];
-      cxin[q] = nxin[q];
-    }
   }
 #pragma unroll
   for (int t = 0; t < NTT; ++t) {
     const int tap = 2 * t + (r >> 3);
     if (tap > 26) continue;
-    const int kcol = tap * cin + grp * 8 + (r & 7);
+    const int kcol = tap * cin + (grp + wave) * 8 + (r & 7);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int co = co0 + 4 * g + i;
       if (co < cg.cout) atomicAdd(dw + static_cast<long long>(co) * cg.kpad + kcol, acc[t][i]);
     }
   }
-  if (bias) {
+  if (bias && wave == 0) {
+    // sum over the 32 staged voxels of each channel half, one atomic per channel
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
 #pragma unroll
-      for (int m = 16; m >= 1; m >>= 1) bacc[j] += __shfl_xor(bacc[j], m, 64);
-    }
-    if (vl == 0) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int co = co0 + 8 * h + j;
-        if (co < cg.cout) atomicAdd(db + co, bacc[j]);
-      }
+      for (int m = 32; m >= 2; m >>= 1) bacc[j] += __shfl_xor(bacc[j], m, 64);
+      const int co = co0 + 8 * h + j;
+      if (lane < 2 && co < cg.cout) atomicAdd(db + co, bacc[j]);
     }
   }
 }
@@ -1384,37 +1417,51 @@ void launch_conv_wgrad(const uint16_t* dz, int cz, const uint16_t* x0, const uin
   // 96 x 112 x 96: longer chunks starve the low-resolution layers)
   const long long vfull = static_cast<long long>(cg.i0) * cg.i1 * cg.i2;
   if (cg.ntaps == 27 && cg.stride == 1 && !cg.dil0 && cg.c0 + cg.c1 >= 16 &&
-      vfull * std::max(cg.c0, cg.c1) < (1LL << 31)) {
+      vfull * std::max(cg.c0, cg.c1) < (1LL << 31) &&
+      6LL * cg.i1 * cg.i2 * std::max(cg.c0, cg.c1) < (1LL << 31) &&
+      10LL * cg.o2 * cz < (1LL << 31)) {
     // all taps of a channel group per wave (measured on the warm-start
     // network at 96 x 112 x 96: faster than the tap-by-tap kernel on its
-    // decoder layers, six or more channel groups, and slightly on its output
-    // layer, two groups; slower on its first layer, one group of 8 channels
-    // of which two are used); K steps per wave doubled from 8 up to 256
-    // while at least 2048 waves remain (longer runs mean fewer atomics on
-    // the same gradient entries)
+    // decoder and output layers, two or more channel groups; slower on its
+    // first layer, one group of 8 channels of which two are used); offsets
+    // within three planes of the input and four rows of dz are 31 bits.  K
+    // steps per wave doubled from 8 up to 256 while at least 1536 waves
+    // remain, so that the 3072 resident at once hold the launch (longer runs
+    // mean fewer atomics on the same gradient entries: the output layer, 2
+    // groups, 445 us in 4032 waves and 337 in 2016; 96 -> 32 at 4 x 48 x 56 x
+    // 48 312 us in 3024, 334 in 2016)
     // Rows per K step: 4 (8 voxels each) where d2 is a multiple of 8, so
     // that no lane of a step falls past the row, else one row of 32
     const int rr = cg.o2 % 8 == 0 ? 4 : 1;
     const uint32_t ngrp = static_cast<uint32_t>((cg.c0 + cg.c1) / 8);
+    // channel groups per block: 4 or 2 where they divide each tensor's
+    // channels, so that a block stages 64 or 32 contiguous bytes per position
+    const uint32_t gb = cg.c0 % 32 == 0 && cg.c1 % 32 == 0   ? 4
+                        : cg.c0 % 16 == 0 && cg.c1 % 16 == 0 ? 2
+                                                             : 1;
     const int wv = 32 / rr;
     const long long nsteps = cg.nvox / (static_cast<long long>(cg.o1) * cg.o2) *
                              ((cg.o1 + rr - 1) / rr) * ((cg.o2 + wv - 1) / wv);
     long long ws = 8;
-    while (ws < 256 && (nsteps + 2 * ws - 1) / (2 * ws) * ngrp * gz >= 2048) ws *= 2;
-    const dim3 grid(static_cast<uint32_t>((nsteps + ws - 1) / ws * ngrp * gz));
+    while (ws < 256 && (nsteps + 2 * ws - 1) / (2 * ws) * ngrp * gz >= 1536) ws *= 2;
+    const dim3 grid(static_cast<uint32_t>((nsteps + ws - 1) / ws * (ngrp / gb * gz)));
     const int w = static_cast<int>(ws);
-    auto go = [&](auto xm, auto rm) {
-      constexpr int XM = decltype(xm)::value, RM = decltype(rm)::value;
-      hipLaunchKernelGGL((k_conv_wgrad_rows<XM, RM>), grid, dim3(64), 0, st, w, dz, cz, x0, x1, cg,
-                         dw, db);
-    };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
     using I4 = std::integral_constant<int, 4>;
+    auto go = [&](auto xm, auto rm, auto gm) {
+      constexpr int XM = decltype(xm)::value, RM = decltype(rm)::value, GM = decltype(gm)::value;
+      hipLaunchKernelGGL((k_conv_wgrad_rows<XM, RM, GM>), grid, dim3(64 * GM), 0, st, w, dz, cz, x0,
+                         x1, cg, dw, db);
+    };
+    auto group = [&](auto xm, auto rm) {
+      if (gb == 4) go(xm, rm, I4{}); else if (gb == 2) go(xm, rm, I2{}); else go(xm, rm, I1{});
+    };
     if (cg.up0) {
-      if (rr == 4) go(I1{}, I4{}); else go(I1{}, I1{});
+      if (rr == 4) group(I1{}, I4{}); else group(I1{}, I1{});
     } else {
-      if (rr == 4) go(I0{}, I4{}); else go(I0{}, I1{});
+      if (rr == 4) group(I0{}, I4{}); else group(I0{}, I1{});
     }
     prof_end(st, KC_MISC);
     return;

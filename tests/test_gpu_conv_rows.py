@@ -77,3 +77,37 @@ def test_infinite_input_stays_in_its_window():
     want = torch.zeros(dims, dtype=torch.bool)
     want[2:5, 3:6, 9:12] = True
     assert bool((bad == want).all())
+
+
+@pytest.mark.parametrize("dims,c0,c1,up,cout", [
+    ((2, 2, 2), 16, 0, False, 16), ((3, 5, 7), 8, 8, False, 3), ((4, 3, 8), 32, 0, False, 17),
+    ((2, 6, 34), 32, 32, True, 16), ((6, 10, 8), 16, 48, True, 33), ((5, 9, 40), 24, 0, False, 8),
+    ((3, 7, 31), 64, 32, False, 24), ((2, 2, 3), 16, 0, False, 8), ((2, 4, 16), 16, 8, True, 40)])
+def test_weight_gradient(dims, c0, c1, up, cout):
+    """Every tap, channel group and output channel at ragged rows and both
+    tensors, against FP64 sums; the bias gradient beside it."""
+    n, cin = 3, c0 + c1
+    x0, x1, w, _, full = operands(dims[2] + 7 * cout, n, dims, c0, c1, up, cout)
+    dev = torch.device("cuda", 0)
+    cz = (cout + 7) // 8 * 8
+    dz = torch.zeros((n,) + dims + (cz,), dtype=torch.bfloat16)
+    dz[..., :cout] = torch.randn((n,) + dims + (cout,), generator=torch.Generator().manual_seed(2)).to(
+        torch.bfloat16)
+    wp = torch.from_numpy(N.pack_weights(w)).to(dev)
+    dw, db, _ = N.conv3d_grad(dz.to(dev), x0.to(dev), wp, cout, x1=None if x1 is None else x1.to(dev),
+                              up0=up, input_grad=False)
+    d = dz.double()[..., :cout]
+    pad = F.pad(full, (0, 0, 1, 1, 1, 1, 1, 1))
+    ref = torch.zeros(cout, 27, cin, dtype=torch.float64)
+    mag = torch.zeros_like(ref)
+    for t in range(27):
+        a, b, c = t // 9, t // 3 % 3, t % 3
+        x = pad[:, a:a + dims[0], b:b + dims[1], c:c + dims[2]].reshape(-1, cin)
+        ref[:, t] = d.reshape(-1, cout).T @ x
+        mag[:, t] = d.abs().reshape(-1, cout).T @ x.abs()
+    got = dw.cpu().double()[:, :27 * cin].view(cout, 27, cin)
+    # FP32 accumulation of every voxel's product, in any order
+    tol = 2 * (n * dims[0] * dims[1] * dims[2] / 32 + 8) * 2.0 ** -24
+    assert bool(((got - ref).abs() <= tol * mag).all())
+    bref = d.reshape(-1, cout).sum(0)
+    assert bool(((db.cpu().double() - bref).abs() <= 2 * tol * 32 * d.abs().reshape(-1, cout).sum(0)).all())
