@@ -2147,16 +2147,16 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, int t, int 
     launch_hat_r<false, false>(ut, gin, gout, hg, n, sc, rc, later, st);
   else
     launch_hat_r<false, true>(ut, gin, gout, hg, n, sc, rc, later, st);
-  prof_end(st, KC_EXP_BWD);
   if (!recs) {
+    prof_end(st, KC_EXP_BWD);
     // (the kernel takes step t > 0 from ckpt + (t - 1) fields)
     AuxPtrs one = ap;
     one.boxes = ap.boxes + ap.box_stride * t;
     one.reach = rc;
     one.box_stride = one.reach_stride = 0;
     launch_rec(ut, ut, 0, first ? 0 : 1, 1, m.rec, sc, one, true, st);
+    prof_begin(st, KC_EXP_BWD);
   }
-  prof_begin(st, KC_EXP_BWD);
   const uint32_t items = m.total > bg.total ? m.total : bg.total;
   if (first)
     hipLaunchKernelGGL((k_exp_bwd_far<true>), dim3(far_grid<true>(items)), dim3(ENT), 0, st, ut,
