@@ -268,12 +268,13 @@ __global__ __launch_bounds__(CNT, ROWS ? (MT == 8 ? 4 : 5) - NT16 : 1) void k_co
   constexpr int NU = (NUNIT + CNT - 1) / CNT;  // per thread
   static_assert(CNT % CG == 0, "a thread's staging units share one channel group");
   static_assert(NU <= 16, "staging flags fit one word");
-  __shared__ uint4 brick[B::NVOX * SU];
+  // ROWS: the chunk's weight fragments follow, [K step][d1 tap][column tile][lane],
+  // then one unit of zeros
+  constexpr int NWF = 15 * NT16, NWU = (NWF * 64 + CNT - 1) / CNT;
+  __shared__ uint4 brick[B::NVOX * SU + (ROWS ? NWF * 64 + 1 : 0)];
+  uint4* const wfrag = brick + B::NVOX * SU;
   // (A byte offset at row tile 0, weight offset) per pair
   __shared__ int2 ktab[ROWS ? 1 : NSTEP * 4];
-  // ROWS: the chunk's weight fragments, [K step][d1 tap][column tile][lane]
-  constexpr int NWF = 15 * NT16, NWU = (NWF * 64 + CNT - 1) / CNT;
-  __shared__ uint4 wfrag[ROWS ? NWF * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kg = lane >> 4;
   // block -> (subject, brick); consecutive bricks of a subject share an XCD
@@ -416,12 +417,17 @@ __global__ __launch_bounds__(CNT, ROWS ? (MT == 8 ? 4 : 5) - NT16 : 1) void k_co
           pre[u] = load_masked16(one ? b1 : b0, one ? uo1[u] : kNoAccess, one ? c : 0u);
       }
     };
-    // per K step: the lane's A offset (row 0)
-    uint32_t ao[5];
+    // per K step: the lane's A offset (row 0).  The tenth tap of the five steps
+    // is none: its weights are zero, and its lanes read zeros in every row, so
+    // that an infinite input meets no zero weight.
+    if (threadIdx.x == 0) wfrag[NWF * 64] = make_uint4(0u, 0u, 0u, 0u);
+    const int row4 = kg < 2 ? B::NX * SU * 16 : 0;  // row stride of the last step
+    int ao[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const int m = min(2 * k + (kg >> 1), 8);
-      ao[k] = static_cast<uint32_t>((m / 3 * B::NY * B::NX + m % 3) * SU * 16 + (kg & 1) * 16);
+      const int m = 2 * k + (kg >> 1);
+      ao[k] = m < 9 ? (m / 3 * B::NY * B::NX + m % 3) * SU * 16 + (kg & 1) * 16
+                    : (B::NVOX - (wave * B::NY * B::NX + r)) * SU * 16 + NWF * 64 * 16;
     }
     // weight fragments staged by this thread: u * CWAVES + wave, its own lane's
     uint32_t wo[NWU];
@@ -459,7 +465,8 @@ __global__ __launch_bounds__(CNT, ROWS ? (MT == 8 ? 4 : 5) - NT16 : 1) void k_co
         uint4 a[MT + 2];
 #pragma unroll
         for (int y = 0; y < MT + 2; ++y)
-          a[y] = *reinterpret_cast<const uint4*>(abase + ao[k] + y * B::NX * SU * 16);
+          a[y] = *reinterpret_cast<const uint4*>(abase + ao[k] +
+                                                 y * (k == 4 ? row4 : B::NX * SU * 16));
 #pragma unroll
         for (int b3 = 0; b3 < 3; ++b3) {
 #pragma unroll

@@ -77,6 +77,9 @@ def test_infinite_input_stays_in_its_window():
     want = torch.zeros(dims, dtype=torch.bool)
     want[2:5, 3:6, 9:12] = True
     assert bool((bad == want).all())
+    # each of those windows holds it once: an infinity of the weight's sign
+    tap = torch.from_numpy(w[:, 7]).flip(1, 2, 3)
+    assert bool((y[0, :, 2:5, 3:6, 9:12] == tap.sign() * float("inf")).all())
 
 
 @pytest.mark.parametrize("dims,c0,c1,up,cout", [
