@@ -116,6 +116,14 @@ __device__ __forceinline__ void flush_reach(int rmax, int* __restrict__ reach, i
 // were taken) a cell beyond reach 1, or it did not try.
 constexpr int kNonFinite = 6, kFar = 7;
 
+// Set and read by blocks of one launch while others do.
+__device__ __forceinline__ void set_mark(int* m) {
+  __hip_atomic_store(m, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int get_mark(const int* m) {
+  return __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ int max_reach(const int* rc) {
   return max(max(max(rc[0], rc[1]), max(rc[2], rc[3])), max(rc[4], rc[5]));
 }
@@ -749,6 +757,7 @@ struct HatLds {
   float uring[3 * HSLOT];  // u_t of planes q-2, q-1, q (slot p % 3)
   float4 src4[HHP];        // plane q: clamped u (scaled in the first step), g0
   float2 src2[HHP];        // g1, g2
+  int skip;                // the block has nothing to do
   int stop;                // a cell beyond reach 1 was staged
 };
 
@@ -828,13 +837,15 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
   const int z0 = static_cast<int>(b % m.nzc) * m.tz, z1 = min(z0 + m.tz, g.d0);
   const int s = static_cast<int>(b / m.nzc);
   if (CHECK) {
-    if (reach[s * 8 + kFar]) return;
-    if (later && max_reach(later + s * 8) >= 4) {
-      if (threadIdx.x == 0) reach[s * 8 + kFar] = 1;
-      return;
+    // one thread reads the mark, which other blocks set meanwhile, for all
+    if (threadIdx.x == 0) {
+      const bool tried = !later || max_reach(later + s * 8) < 4;
+      if (!tried) set_mark(reach + s * 8 + kFar);
+      L.skip = !tried || get_mark(reach + s * 8 + kFar);
+      L.stop = 0;
     }
-    if (threadIdx.x == 0) L.stop = 0;
     __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(L.skip)) return;
   } else if (max_reach(reach + s * 8) > 1) {
     return;
   }
@@ -932,7 +943,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
     load_plane(q + 1);
     __syncthreads();
     if (CHECK && __builtin_amdgcn_readfirstlane(L.stop)) {
-      if (tid == 0) reach[s * 8 + kFar] = 1;
+      if (tid == 0) set_mark(reach + s * 8 + kFar);
       return;
     }
     const int p = q - 1;  // the target plane finished by this step
@@ -1016,7 +1027,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
     }
     __syncthreads();
   } while (++q <= z1);
-  if (bad) reach[s * 8 + kNonFinite] = 1;
+  if (bad) set_mark(reach + s * 8 + kNonFinite);
 }
 
 // The same gather without marching, for volumes too small to fill the chip with
