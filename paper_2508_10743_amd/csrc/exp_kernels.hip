@@ -751,8 +751,8 @@ __device__ __forceinline__ void exp_bwd_tile(TiledBwdLds& L, int s, int tile,
 //
 // A source contributes to the eight corners of its cell only, so a target
 // next to it must not see 0 * g when g is not finite.  A block that meets
-// such a g says so in its subject's record (kNonFinite), and the tiled kernel,
-// launched after this one, then computes that subject again.
+// such a g says so in its subject's record (kNonFinite), and the reach-2
+// kernel, launched after this one, then computes that subject again.
 struct HatLds {
   float uring[3 * HSLOT];  // u_t of planes q-2, q-1, q (slot p % 3)
   float4 src4[HHP];        // plane q: clamped u (scaled in the first step), g0
@@ -1591,15 +1591,17 @@ __device__ __forceinline__ void exp_bwd_march2(March2Lds& L, const MarchGeom& m,
 
 // The subjects that the reach-1 adjoint does not take, in one launch (an idle
 // launch costs as much as a small step): the first half of the blocks walks the
-// column chunks of subjects with reach 2, the second half the tiles of those
-// with a cell offset beyond [-2, 1], of those whose gradient is not finite, and
-// of those that the reach-1 adjoint left without need (kFar with reach 1).
-// Both halves step through the work together, block b taking items b,
-// b + half, ..., so that the items in flight are neighbours (those of one XCD a
-// contiguous range) and every block has a share of each subject.
-__device__ __forceinline__ bool needs_tiled(const int* rc) {
+// column chunks of subjects with reach 2, and of those with reach 1 that the
+// reach-1 adjoint left or whose gradient is not finite (the cell bins carry any
+// gradient to the eight corners of its cell only); the second half the tiles of
+// those with a cell offset beyond [-2, 1].  The reach alone separates the two,
+// so that no subject is written by both.  Both halves step through the work
+// together, block b taking items b, b + half, ..., so that the items in flight
+// are neighbours (those of one XCD a contiguous range) and every block has a
+// share of each subject.
+__device__ __forceinline__ bool takes_far(const int* rc, bool tiled) {
   const int mr = max_reach(rc);
-  return mr > 2 || rc[kNonFinite] || (rc[kFar] && mr <= 1);
+  return tiled ? mr > 2 : mr == 2 || (mr < 2 && (rc[kNonFinite] || rc[kFar]));
 }
 
 union FarLds {
@@ -1623,22 +1625,21 @@ __global__ __launch_bounds__(ENT, 3) void k_exp_bwd_far(const float* __restrict_
     const int nsub = static_cast<int>(bg.total / bg.ntiles);
     int any = 0;
     for (int q = threadIdx.x; q < nsub; q += ENT) {
-      const int* rc = reach + q * 8;
-      any |= tiled ? needs_tiled(rc) : max_reach(rc) == 2;
+      any |= takes_far(reach + q * 8, tiled);
     }
     if (!__syncthreads_or(any)) return;
   }
   if (tiled) {
     for (uint32_t b = xcd_remap(blockIdx.x - half, half); b < bg.total; b += half) {
       const int s = static_cast<int>(b / bg.ntiles);
-      if (needs_tiled(reach + s * 8))
+      if (takes_far(reach + s * 8, true))
         exp_bwd_tile<FIRST>(L.tiled, s, static_cast<int>(b - static_cast<uint32_t>(s) * bg.ntiles),
                             ut, gin, gout, bg, scale, oscale, boxes, reach);
     }
   } else {
     for (uint32_t b = xcd_remap(blockIdx.x, half); b < m.total; b += half) {
       const MarchId id = march_id_at(m, b);
-      if (max_reach(reach + id.s * 8) == 2)
+      if (takes_far(reach + id.s * 8, false))
         exp_bwd_march2<FIRST>(L.march2, m, id, ut, gin, gout, scale, oscale);
     }
   }
