@@ -744,9 +744,9 @@ __device__ __forceinline__ void exp_bwd_tile(TiledBwdLds& L, int s, int tile,
 // vector instructions) took 1.40 ms.  16 x 160 x 192 x 160: 0.76 and 0.95 ms.
 //
 // Border clamping moves a source whose position leaves the volume onto its
-// face: the staged u is clamped to [-1, 1] (a voxel next to a face may point
-// outwards by any amount and still have its cell within reach 1), and to
-// zero outwards on a face.  Positions outside the volume are staged with
+// face: the staged u of the two layers at a face is clamped to what stays inside
+// (a voxel there may point outwards by any amount and still have its cell within
+// reach 1).  Positions outside the volume are staged with
 // g = 0.
 //
 // A source contributes to the eight corners of its cell only, so a target
@@ -802,24 +802,31 @@ __device__ __forceinline__ void hat_pairs(const HatLds& L, int at, float (&s0)[2
 }
 
 // Range of the displacement along one axis that stays inside the volume, as
-// two bytes (-lo, hi), each 0 or 1: a position within reach 1 is clamped to
+// two bytes (-lo, hi), each at most 2: a position within reach 1 is clamped to
 // [x + lo, x + hi].
 __device__ __forceinline__ uint32_t hat_range(int x, int D) {
-  return static_cast<uint32_t>(x > 0) | (static_cast<uint32_t>(x < D - 1) << 8);
+  return static_cast<uint32_t>(min(max(x, 0), 2)) |
+         (static_cast<uint32_t>(min(max(D - 1 - x, 0), 2)) << 8);
 }
 __device__ __forceinline__ float hat_clamp(float u, uint32_t range) {
   return __builtin_amdgcn_fmed3f(u, -static_cast<float>(range & 255u),
                                  static_cast<float>((range >> 8) & 255u));
+}
+// Whether the cell of a clamped displacement lies beyond reach 1.  (One voxel
+// before the far face a clamped +1 lies in the last cell, at fraction 1; a NaN
+// is clamped to the low end, as everywhere.)
+__device__ __forceinline__ bool hat_beyond(float w, uint32_t range) {
+  return w < -1.0f || (w >= 1.0f && ((range >> 8) & 255u) == 2u);
 }
 
 // CHECK: the forward took no records.  The kernel then looks at the
 // displacements it stages; a block that meets a cell beyond reach 1 marks the
 // subject (kFar) and ends, and the records of marked subjects are taken
 // afterwards for the other adjoints.  `later` (or NULL) are the reaches of the
-// step after this one, walked before it: displacements about double per step,
-// so a subject with a reach of 4 or more there is marked without a try.  (A
-// voxel next to a face that points outwards by more than one voxel is marked
-// too, though its clamped cell is within reach: the tiled kernel takes it.)
+// step after this one, walked before it: a subject with a reach of 4 or more
+// there is marked without a try, since a step of reach 1 gives one of at most 2
+// (two displacements in [-1, 1) add up to one in [-2, 2); more than one voxel
+// outwards occurs only beside a face, where the clamped cells stay within 2).
 template <bool FIRST, bool CHECK, bool STREAM>
 __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict__ ut,
                                                         const float* __restrict__ gin,
@@ -924,9 +931,14 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
         u[0] = hat_clamp(u[0], rz);
         u[1] = hat_clamp(u[1], prange[j] >> 16);
         u[2] = hat_clamp(u[2], prange[j]);
+        if (CHECK && (hat_beyond(u[0], rz) || hat_beyond(u[1], prange[j] >> 16) ||
+                      hat_beyond(u[2], prange[j])))
+          L.stop = 1;
+      } else if (CHECK && !(u[0] >= -1.0f && u[0] < 1.0f && u[1] >= -1.0f && u[1] < 1.0f &&
+                            u[2] >= -1.0f && u[2] < 1.0f)) {
+        L.stop = 1;
       }
       bad |= !__builtin_isfinite(pg[j][0] + pg[j][1] + pg[j][2]);
-      if (CHECK && !(fabsf(u[0]) < 1.0f && fabsf(u[1]) < 1.0f && fabsf(u[2]) < 1.0f)) L.stop = 1;
       L.src4[e] = make_float4(u[0], u[1], u[2], pg[j][0]);
       L.src2[e] = make_float2(pg[j][1], pg[j][2]);
     }
@@ -974,7 +986,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
             const float w = hat_clamp(u[c], rg[c]);
             kl[c] = w != u[c];
             u[c] = w;
-            lo[c] = w < 1.0f - static_cast<float>((rg[c] >> 8) & 255u);
+            lo[c] = w < (((rg[c] >> 8) & 255u) ? 0.0f : 1.0f);
           }
         }
         const float f0 = u[0] + (lo[0] ? 1.0f : 0.0f), f1 = u[1] + (lo[1] ? 1.0f : 0.0f),

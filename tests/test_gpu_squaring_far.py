@@ -81,3 +81,28 @@ def test_non_finite_gradient_away_from_far_cells(bad):
         assert np.array_equal(got[i][far], again[i][far])
         if peaks[i] in (1.4, -1.7):
             assert np.array_equal(got[i][far], clean[i][far])
+
+
+def test_outward_faces_stay_with_the_reach_1_kernel():
+    """Voxels on and beside the faces that point outwards by any amount, and -1
+    itself, have their cells within reach 1; +1 in the interior does not.  The
+    kernel shows in the rounding: a bad gradient elsewhere sends a subject of
+    reach 1 to the reach-2 kernel, which takes one of reach 2 in any case."""
+    dims = (27, 35, 50)
+    u, gr = step(dims, [-0.3, -0.3])
+    for c in range(3):
+        f = np.moveaxis(u[:, c], c + 1, 1)
+        f[:, 0], f[:, 1], f[:, -2], f[:, -1] = -5.5, -3.5, 2.5, 7.25
+    u[:, :, 9, 15:18, 20:30] = -1.0
+    u[1, 2, 14, 20, 25] = 1.0
+    hurt = gr.copy()
+    hurt[:, 0, 22, 9, 17] = np.nan
+    v = torch.from_numpy(u * 2.0).cuda()
+    clean = D.exp_svf_bwd(v, None, torch.from_numpy(gr).cuda(), 1).cpu().numpy()
+    other = D.exp_svf_bwd(v, None, torch.from_numpy(hurt).cuda(), 1).cpu().numpy()
+    for i in range(2):
+        ref = O.squaring_step_bwd(u[i], gr[i]) * 0.5
+        assert np.linalg.norm(clean[i] - ref) <= TOL * np.linalg.norm(ref)
+        assert np.isfinite(clean[i]).all() and not np.isfinite(other[i]).all()
+        inner = np.s_[:, 4:8, 4:-4, 4:-4]  # one source in each cell
+        assert np.array_equal(clean[i][inner], other[i][inner]) == (i == 1)
