@@ -105,12 +105,13 @@ __device__ __forceinline__ void write_record(int mn0, int mn1, int mn2, int mx0,
   }
 }
 
-// Set and read by blocks of one launch while others do.
-__device__ __forceinline__ void set_mark(int* m) {
-  __hip_atomic_store(m, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// Set and read by blocks of one launch while others do.  A mark that stands is
+// not stored again: the stores of a subject's blocks queue up at its line.
 __device__ __forceinline__ int get_mark(const int* m) {
   return __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void set_mark(int* m) {
+  if (!get_mark(m)) __hip_atomic_store(m, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The block's reaches into the subject's: thread q < 6 holds entry q.  Atomics
@@ -851,7 +852,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
     // one thread reads the mark, which other blocks set meanwhile, for all
     if (threadIdx.x == 0) {
       const bool tried = !later || max_reach(later + s * 8) < 4;
-      if (!tried) set_mark(reach + s * 8 + kFar);
+      if (!tried && ox == 0 && oy == 0 && z0 == 0) set_mark(reach + s * 8 + kFar);
       L.skip = !tried || get_mark(reach + s * 8 + kFar);
       L.stop = 0;
     }
