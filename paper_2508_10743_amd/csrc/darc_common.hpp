@@ -284,8 +284,16 @@ __device__ __forceinline__ void store_masked(const MaskedOut& m, uint32_t i, flo
 // next kernel cannot find them there anyway, and they leave room for the halos
 // that neighbouring blocks share.  16 x 160 x 192 x 224: squaring step 0.62 ->
 // 0.60 ms, its adjoint 1.17 -> 1.16, the Gaussian 0.75 -> 0.73; an output that
-// fits loses (4 x 96 x 112 x 96: Exp and its gradient 0.8 % slower).
+// fits loses (4 x 96 x 112 x 96: Exp and its gradient 0.8 % slower).  Only where
+// the kernels' rows of 32 voxels consist of whole 64-byte pieces: a piece that
+// two blocks write in parts goes to memory in parts.  Seven squaring steps of 16
+// subjects, plain and with STREAM: 160 x 192 x 176 4.00 and 3.72 ms; x 168 4.48
+// and 5.65; 182 x 218 x 182 6.54 and 9.47 (the Gaussian there 0.89 and 1.24).
 constexpr size_t kStreamBytes = static_cast<size_t>(256) << 20;
+inline bool streamed(const float* out, size_t count, const Geom& g) {
+  return count * sizeof(float) > kStreamBytes && g.d2 % 16 == 0 &&
+         reinterpret_cast<uintptr_t>(out) % 64 == 0;
+}
 
 // Loads through the same range check: byte offsets of kNoAccess or more
 // return zero without a memory access.

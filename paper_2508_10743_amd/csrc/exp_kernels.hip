@@ -2027,8 +2027,7 @@ namespace {
 template <bool FIRST, bool REC>
 void launch_exp_fwd_r(const float* src, float* dst, const HatGeom& hg, const TileGeom& tg,
                       float scale, int* bx, int* rc, hipStream_t st) {
-  const size_t out = static_cast<size_t>(tg.total / tg.ntiles) * 3 * tg.g.V * sizeof(float);
-  if (out > kStreamBytes)
+  if (streamed(dst, static_cast<size_t>(tg.total / tg.ntiles) * 3 * tg.g.V, tg.g))
     hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, true>), dim3(hg.total), dim3(ENT), 0, st, src, dst,
                        hg, tg, scale, bx, rc);
   else
@@ -2052,7 +2051,7 @@ void launch_exp_fwd(const float* src, float* dst, bool first, const HatGeom& hg,
 template <bool FIRST, bool CHECK>
 void launch_hat_r(const float* ut, const float* gin, float* gout, const HatGeom& hg, int n,
                   float scale, int* rc, const int* later, hipStream_t st) {
-  if (static_cast<size_t>(n) * 3 * hg.g.V * sizeof(float) > kStreamBytes)
+  if (streamed(gout, static_cast<size_t>(n) * 3 * hg.g.V, hg.g))
     hipLaunchKernelGGL((k_exp_bwd_hat<FIRST, CHECK, true>), dim3(hg.total), dim3(ENT), 0, st, ut,
                        gin, gout, hg, scale, scale, rc, later);
   else

@@ -352,7 +352,7 @@ void launch_warp(const float* img, const float* u, float* out, const Geom& g, in
 void launch_warp_bwd(const float* img, const float* u, const float* gout, float* gu, bool acc,
                      const Geom& g, int n, hipStream_t st) {
   const WarpGrid w = make_warp_grid(g, n);
-  const bool stream = static_cast<size_t>(n) * 3 * g.V * sizeof(float) > kStreamBytes;
+  const bool stream = streamed(gu, static_cast<size_t>(n) * 3 * g.V, g);
   prof_begin(st, KC_WARP_BWD);
   if (acc && stream)
     hipLaunchKernelGGL((k_warp_bwd<true, true>), dim3(w.total), dim3(kWarpNT), 0, st, img, u, gout,

@@ -696,7 +696,7 @@ template <int R>
 void gauss_r(const float* in, float* out, const GaussW& gw, const Geom& g, int nchan,
              hipStream_t st) {
   const MarchGeom mg = make_march(g, nchan, R, kGX, kNT * gauss_rows(R) / kGX);
-  if (static_cast<size_t>(nchan) * g.V * sizeof(float) > kStreamBytes)
+  if (streamed(out, static_cast<size_t>(nchan) * g.V, g))
     hipLaunchKernelGGL((k_gauss<R, true>), dim3(mg.total), dim3(kNT), 0, st, in, out, mg, gw);
   else
     hipLaunchKernelGGL((k_gauss<R, false>), dim3(mg.total), dim3(kNT), 0, st, in, out, mg, gw);
