@@ -226,16 +226,24 @@ __device__ __forceinline__ MarchId march_id_at(const MarchGeom& m, uint32_t b) {
   return id;
 }
 
-// Columns of the marching squaring step and of its reach-1 adjoint: 32 x 16,
-// two adjacent rows per thread, a one-voxel halo staged in LDS.
-constexpr int HTY = 16;
-constexpr int HHX = ETX + 2, HHY = HTY + 2;    // staged plane with halo: 34 x 18
-constexpr int HHP = HHX * HHY;                 // 612 positions
-constexpr int HRING = HHP - 2 * ENT;           // halo positions (100)
-// One plane of the ring of u, its components HHP apart, padded to a multiple of
-// the 64 LDS banks: lanes of a row whose cells lie in different planes then
-// read different banks.
-constexpr int HSLOT = (3 * HHP + 63) / 64 * 64;
+// Columns of the marching squaring step and of its reach-1 adjoint: ROWS
+// adjacent rows per thread (32 x 8 or 32 x 16 voxels), a one-voxel halo staged
+// in LDS.
+constexpr int HHX = ETX + 2;
+template <int ROWS>
+struct Column {
+  static constexpr int TY = ROWS * ETY;
+  static constexpr int HY = TY + 2;               // staged plane with halo: 34 x 10 or 34 x 18
+  static constexpr int HP = HHX * HY;             // 340 or 612 positions
+  // One plane of the ring of u, its components HP apart, padded to a multiple
+  // of the 64 LDS banks: lanes of a row whose cells lie in different planes then
+  // read different banks.
+  static constexpr int SLOT = (3 * HP + 63) / 64 * 64;
+};
+// The adjoint's columns.
+constexpr int HTY = Column<2>::TY, HHY = Column<2>::HY, HHP = Column<2>::HP,
+              HSLOT = Column<2>::SLOT;
+constexpr int HRING = HHP - 2 * ENT;  // its halo positions (100)
 
 struct HatGeom {
   Geom g;
@@ -243,11 +251,11 @@ struct HatGeom {
   uint32_t total;
 };
 
-HatGeom make_hat(const TileGeom& tg, int tz) {
+HatGeom make_hat(const TileGeom& tg, int tz, int ty) {
   HatGeom h;
   h.g = tg.g;
   h.ntx = tg.ntx;
-  h.nty = (tg.g.d1 + HTY - 1) / HTY;
+  h.nty = (tg.g.d1 + ty - 1) / ty;
   h.tz = tz;
   h.nzc = (tg.g.d0 + tz - 1) / tz;
   h.total = static_cast<uint32_t>(h.ntx) * h.nty * h.nzc * (tg.total / tg.ntiles);
@@ -269,10 +277,11 @@ __device__ __forceinline__ void ring_position(int tid, int& hy, int& hx) {
 // As many (discarded) stores after the loads of the loop's first plane as every
 // step issues after its loads, so that the wait at the head of the loop counts
 // the same on both ways in and leaves the stores in flight.
+template <int ROWS>
 __device__ __forceinline__ void discarded_stores(const MaskedOut (&out)[3]) {
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) store_masked(out[k % 3], 0u, 0.0f, false);
+  for (int k = 0; k < 3 * ROWS; ++k) store_masked(out[k % 3], 0u, 0.0f, false);
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -283,16 +292,18 @@ __device__ __forceinline__ void discarded_stores(const MaskedOut (&out)[3]) {
 // come from LDS; bound by the memory system (1.4x the input fetched, the halo
 // lines that L2 no longer holds; neither fewer instructions nor a second plane
 // in flight changed its time).  16 x 160 x 192 x 224: 0.60 ms, 4.4 TB/s; on
-// 32 x 8 columns with every cell formed in full 0.65.  Away from the faces and with |u| < 1 a voxel's cell is at
-// -1 or 0 by the sign of u; other voxels take the general cell, with corners
-// from memory where they leave the staged planes.  Records start at offsets
-// [-1, 0] and grow with those other voxels only.
-template <bool FIRST, bool REC, bool STREAM>
+// 32 x 8 columns with every cell formed in full 0.65.  With |u| < 1 a voxel's cell
+// is at -1 or 0 by the sign of u, clamped at the faces by a median; other voxels
+// take the general cell, with corners from memory where they leave the staged
+// planes.  Records start at offsets [-1, 0] and grow with those other voxels
+// only.
+template <bool FIRST, bool REC, bool STREAM, int ROWS>
 __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
                                                  float* __restrict__ dst, HatGeom m, TileGeom rec,
                                                  float scale, int* __restrict__ boxes,
                                                  int* __restrict__ reach) {
-  __shared__ float ring[3 * HSLOT];
+  using C = Column<ROWS>;
+  __shared__ float ring[3 * C::SLOT];
   __shared__ int red[6][ENT / 64];
   const Geom& g = m.g;
   uint32_t b = xcd_remap(blockIdx.x, m.total);
@@ -302,7 +313,7 @@ __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
   b /= m.nty;
   const int z0 = static_cast<int>(b % m.nzc) * m.tz, z1 = min(z0 + m.tz, g.d0);
   const int s = static_cast<int>(b / m.nzc);
-  const int ox = tx * ETX, oy = ty * HTY;
+  const int ox = tx * ETX, oy = ty * C::TY;
   const size_t off = static_cast<size_t>(s) * 3 * g.V;
   MaskedOut out[3];
   MaskedIn in[3];
@@ -312,39 +323,50 @@ __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
     out[c] = masked_out(dst + off + static_cast<size_t>(c) * g.V, static_cast<uint32_t>(g.V));
   }
   const int tid = threadIdx.x, lx = tid % ETX, ry = tid / ETX;
-  const int x2 = ox + lx, y1 = oy + 2 * ry;
-  const int at = (2 * ry + 1) * HHX + lx + 1;  // staged position of the first voxel
-  int pr;
-  uint32_t poff[3];
-  {
-    int hy, hx;
-    ring_position(tid, hy, hx);
-    pr = hy * HHX + hx;
+  const int x2 = ox + lx, y1 = oy + ROWS * ry;
+  const int at = (ROWS * ry + 1) * HHX + lx + 1;  // staged position of the first voxel
+  // Staged positions of this thread.  ROWS = 1: tid + j ENT, so that loads run
+  // along whole rows with their halo, and rows off the line grid ask once for the
+  // lines that they share with it.  ROWS = 2: its own two and, for the first
+  // threads, one of the halo ring, so that loads of own rows are whole lines.
+  constexpr int NP = (C::HP + ENT - 1) / ENT;
+  uint32_t poff[NP];
+  int pe[NP];
+  const bool last = tid < C::HP - (NP - 1) * ENT;  // the thread has a last position
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const int y = j < 2 ? y1 + j : oy - 1 + hy, x = j < 2 ? x2 : ox - 1 + hx;
-      const bool inside = y >= 0 && y < g.d1 && x >= 0 && x < g.d2 && (j < 2 || tid < HRING);
-      poff[j] = inside ? static_cast<uint32_t>(y * g.d2 + x) << 2 : kNoAccess;
+  for (int j = 0; j < NP; ++j) {
+    int hy, hx;
+    if (ROWS == 1) {
+      hy = (tid + j * ENT) / HHX;
+      hx = tid + j * ENT - hy * HHX;
+    } else if (j < ROWS) {
+      hy = 1 + ROWS * ry + j;
+      hx = 1 + lx;
+    } else {
+      ring_position(tid, hy, hx);
     }
+    pe[j] = hy * HHX + hx;
+    const int y = oy - 1 + hy, x = ox - 1 + hx;
+    const bool inside = y >= 0 && y < g.d1 && x >= 0 && x < g.d2 && (j + 1 < NP || last);
+    poff[j] = inside ? static_cast<uint32_t>(y * g.d2 + x) << 2 : kNoAccess;
   }
-  const bool rg = tid < HRING;
-  // the column or its halo touches a face of the volume in d1 or d2
-  const bool face = oy == 0 || ox == 0 || oy + HTY >= g.d1 - 1 || ox + ETX >= g.d2 - 1;
-  float pre[3][3];
+  const float far2 = static_cast<float>(x2 >= g.d2 - 1);  // 1 on the far face, else 0
+  const float low2 = x2 > 0 ? -1.0f : 0.0f;
+  float pre[NP][3];
   auto load_plane = [&](int z) {  // planes outside the volume are loaded clamped
     const uint32_t zo = static_cast<uint32_t>(min(max(z, 0), g.d0 - 1) * g.plane) << 2;
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < NP; ++j)
 #pragma unroll
       for (int c = 0; c < 3; ++c) pre[j][c] = load_masked(in[c], zo + poff[j]);
   };
   auto stage = [&](int z) {
-    float* r = ring + (z + 3) % 3 * HSLOT;
+    float* r = ring + (z + 3) % 3 * C::SLOT;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      r[c * HHP + at] = pre[0][c];
-      r[c * HHP + at + HHX] = pre[1][c];
-      if (rg) r[c * HHP + pr] = pre[2][c];
+#pragma unroll
+      for (int j = 0; j < NP; ++j)
+        if (j + 1 < NP || last) r[c * C::HP + pe[j]] = pre[j][c];
     }
   };
   load_plane(z0 - 1);
@@ -352,7 +374,7 @@ __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
   load_plane(z0);
   stage(z0);
   load_plane(z0 + 1);
-  discarded_stores(out);
+  discarded_stores<ROWS>(out);
   int mn[3] = {-1, -1, -1}, mx[3] = {0, 0, 0};
   int rmax = 0;
   int z = z0;
@@ -361,72 +383,77 @@ __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
     load_plane(z + 2);
     __syncthreads();
     const float* r0 = ring;
-    const int slm = (z + 2) % 3 * HSLOT, slc = z % 3 * HSLOT, slp = (z + 1) % 3 * HSLOT;
-    const bool edge = face || z == 0 || z >= g.d0 - 1;
+    const int slm = (z + 2) % 3 * C::SLOT, slc = z % 3 * C::SLOT, slp = (z + 1) % 3 * C::SLOT;
+    const float far0 = static_cast<float>(z >= g.d0 - 1), low0 = z > 0 ? -1.0f : 0.0f;
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int own = at + r * HHX;
-      float u[3], res[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        u[c] = r0[slc + c * HHP + own];
-        if (FIRST) u[c] *= scale;
-      }
-      const bool live = x2 < g.d2 && y1 + r < g.d1;
-      const bool near = !edge && fabsf(u[0]) < 1.0f && fabsf(u[1]) < 1.0f && fabsf(u[2]) < 1.0f;
-      bool lo0 = u[0] < 0.0f, lo1 = u[1] < 0.0f, lo2 = u[2] < 0.0f;
-      float t0 = u[0] + (lo0 ? 1.0f : 0.0f), t1 = u[1] + (lo1 ? 1.0f : 0.0f),
-            t2 = u[2] + (lo2 ? 1.0f : 0.0f);
-      int pb = own + (lo1 ? -HHX : 0) + (lo2 ? -1 : 0);
-      bool ringed = near || !live;
-      int base = 0;
-      if (!near && live) {
-        const BorderCell bc = border_cell(g, z, y1 + r, x2, u[0], u[1], u[2]);
-        const int c0 = bc.i0 - z, c1 = bc.i1 - oy + 1, c2 = bc.i2 - ox + 1;
-        ringed = c0 >= -1 && c0 <= 0 && c1 >= 0 && c1 + 1 < HHY && c2 >= 0 && c2 + 1 < HHX;
-        lo0 = c0 < 0;
-        pb = c1 * HHX + c2;
-        base = bc.base;
-        t0 = bc.t0;
-        t1 = bc.t1;
-        t2 = bc.t2;
-        if (REC) {
-          mn[0] = min(mn[0], c0);
-          mn[1] = min(mn[1], bc.i1 - (y1 + r));
-          mn[2] = min(mn[2], bc.i2 - x2);
-          mx[0] = max(mx[0], c0);
-          mx[1] = max(mx[1], bc.i1 - (y1 + r));
-          mx[2] = max(mx[2], bc.i2 - x2);
-        }
-      }
-      if (ringed) {
-        const float* ra = r0 + (pb + (lo0 ? slm : slc));
-        const float* rb = r0 + (pb + (lo0 ? slc : slp));
+    for (int r = 0; r < ROWS; ++r) {
+      const int own = at + r * HHX, y = y1 + r;
+      const bool live = x2 < g.d2 && y < g.d1;
+      float u[3] = {}, res[3] = {};
+      if (live) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const float cv[8] = {ra[c * HHP],       ra[c * HHP + 1],
-                               ra[c * HHP + HHX], ra[c * HHP + HHX + 1],
-                               rb[c * HHP],       rb[c * HHP + 1],
-                               rb[c * HHP + HHX], rb[c * HHP + HHX + 1]};
-          res[c] = tri_value(cv, t0, t1, t2);
+          u[c] = r0[slc + c * C::HP + own];
+          if (FIRST) u[c] *= scale;
         }
-      } else {
+        const float far1 = static_cast<float>(y >= g.d1 - 1), low1 = y > 0 ? -1.0f : 0.0f;
+        const float w0 = __builtin_amdgcn_fmed3f(u[0], low0, 1.0f - far0),
+                    w1 = __builtin_amdgcn_fmed3f(u[1], low1, 1.0f - far1),
+                    w2 = __builtin_amdgcn_fmed3f(u[2], low2, 1.0f - far2);
+        bool lo0 = w0 < far0, lo1 = w1 < far1, lo2 = w2 < far2;
+        float t0 = w0 + (lo0 ? 1.0f : 0.0f), t1 = w1 + (lo1 ? 1.0f : 0.0f),
+              t2 = w2 + (lo2 ? 1.0f : 0.0f);
+        int pb = own + (lo1 ? -HHX : 0) + (lo2 ? -1 : 0);
+        bool ringed = true;
+        int base = 0;
+        if (!(fabsf(u[0]) < 1.0f && fabsf(u[1]) < 1.0f && fabsf(u[2]) < 1.0f)) {
+          const BorderCell bc = border_cell(g, z, y, x2, u[0], u[1], u[2]);
+          const int c0 = bc.i0 - z, c1 = bc.i1 - oy + 1, c2 = bc.i2 - ox + 1;
+          ringed = c0 >= -1 && c0 <= 0 && c1 >= 0 && c1 + 1 < C::HY && c2 >= 0 && c2 + 1 < HHX;
+          lo0 = c0 < 0;
+          pb = c1 * HHX + c2;
+          base = bc.base;
+          t0 = bc.t0;
+          t1 = bc.t1;
+          t2 = bc.t2;
+          if (REC) {
+            mn[0] = min(mn[0], c0);
+            mn[1] = min(mn[1], bc.i1 - y);
+            mn[2] = min(mn[2], bc.i2 - x2);
+            mx[0] = max(mx[0], c0);
+            mx[1] = max(mx[1], bc.i1 - y);
+            mx[2] = max(mx[2], bc.i2 - x2);
+          }
+        }
+        if (ringed) {
+          const float* ra = r0 + (pb + (lo0 ? slm : slc));
+          const float* rb = r0 + (pb + (lo0 ? slc : slp));
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          float cv[8];
-          corners_border(src + off + c * static_cast<size_t>(g.V), g, base, cv);
-          res[c] = tri_value(cv, t0, t1, t2);
+          for (int c = 0; c < 3; ++c) {
+            const float cv[8] = {ra[c * C::HP],       ra[c * C::HP + 1],
+                                 ra[c * C::HP + HHX], ra[c * C::HP + HHX + 1],
+                                 rb[c * C::HP],       rb[c * C::HP + 1],
+                                 rb[c * C::HP + HHX], rb[c * C::HP + HHX + 1]};
+            res[c] = tri_value(cv, t0, t1, t2);
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            float cv[8];
+            corners_border(src + off + c * static_cast<size_t>(g.V), g, base, cv);
+            res[c] = tri_value(cv, t0, t1, t2);
+          }
         }
       }
-      const uint32_t lin = static_cast<uint32_t>(z * g.plane + (y1 + r) * g.d2 + x2);
+      const uint32_t lin = static_cast<uint32_t>(z * g.plane + y * g.d2 + x2);
 #pragma unroll
       for (int c = 0; c < 3; ++c)
         store_masked<STREAM>(out[c], lin, FIRST ? fmaf(res[c], scale, u[c]) : u[c] + res[c], live);
     }
     if (REC && ((z + 1) % ETZ == 0 || z + 1 == z1)) {
-      // the box entries over each half's two waves; thread q of 12 finishes
-      // entry q % 6 of half q / 6 and folds its reach into a running maximum
-      // (issued once per block)
+      // the box entries over the waves of each record tile (ROWS per column);
+      // thread q finishes entry q % 6 of tile q / 6 and folds its reach into a
+      // running maximum (issued once per block)
       const int lane = tid & 63, w = tid >> 6;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
@@ -439,12 +466,15 @@ __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
         mx[d] = 0;
       }
       __syncthreads();
-      if (tid < 12) {
+      if (tid < 6 * ROWS) {
+        constexpr int NW = ENT / 64 / ROWS;
         const int q = tid % 6, hf = tid / 6;
-        const int a = red[q][2 * hf], c = red[q][2 * hf + 1];
-        const int v = q < 3 ? min(a, c) : max(a, c);
-        if (oy + 8 * hf < g.d1) {
-          const int tile = ((z / ETZ) * rec.nty + 2 * ty + hf) * rec.ntx + tx;
+        int v = red[q][NW * hf];
+#pragma unroll
+        for (int i = 1; i < NW; ++i)
+          v = q < 3 ? min(v, red[q][NW * hf + i]) : max(v, red[q][NW * hf + i]);
+        if (oy + ETY * hf < g.d1) {
+          const int tile = ((z / ETZ) * rec.nty + ROWS * ty + hf) * rec.ntx + tx;
           boxes[(static_cast<size_t>(s) * rec.ntiles + tile) * 8 + q] = v;
           rmax = max(rmax, q < 3 ? -v : v + 1);
         }
@@ -453,7 +483,7 @@ __global__ __launch_bounds__(ENT) void k_exp_fwd(const float* __restrict__ src,
       __syncthreads();
     }
   } while (++z < z1);
-  if (REC && tid < 12 && rmax > 1) atomicMax(reach + s * 8 + tid % 6, rmax);
+  if (REC && tid < 6 * ROWS && rmax > 1) atomicMax(reach + s * 8 + tid % 6, rmax);
 }
 
 // Adjoint tiles: 4 (d0) x 4 (d1) x 32 (d2) output voxels, two per thread.
@@ -950,7 +980,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
   };
 
   load_plane(z0 - 1);
-  discarded_stores(out);
+  discarded_stores<2>(out);
   // twice the partial sums of the targets of planes q - 1 and q
   float accA[2][3] = {}, accB[2][3] = {};
   float og[2][3] = {};  // g of the targets of plane q - 1
@@ -2024,27 +2054,46 @@ bool plane_mode(const Geom& g, int n) {
 namespace {
 
 // One marching squaring step (records when bx is given).
-template <bool FIRST, bool REC>
+template <bool FIRST, bool REC, int ROWS>
 void launch_exp_fwd_r(const float* src, float* dst, const HatGeom& hg, const TileGeom& tg,
                       float scale, int* bx, int* rc, hipStream_t st) {
   if (streamed(dst, static_cast<size_t>(tg.total / tg.ntiles) * 3 * tg.g.V, tg.g))
-    hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, true>), dim3(hg.total), dim3(ENT), 0, st, src, dst,
-                       hg, tg, scale, bx, rc);
+    hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, true, ROWS>), dim3(hg.total), dim3(ENT), 0, st, src,
+                       dst, hg, tg, scale, bx, rc);
   else
-    hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, false>), dim3(hg.total), dim3(ENT), 0, st, src, dst,
-                       hg, tg, scale, bx, rc);
+    hipLaunchKernelGGL((k_exp_fwd<FIRST, REC, false, ROWS>), dim3(hg.total), dim3(ENT), 0, st, src,
+                       dst, hg, tg, scale, bx, rc);
 }
 
-void launch_exp_fwd(const float* src, float* dst, bool first, const HatGeom& hg,
-                    const TileGeom& tg, float scale, int* bx, int* rc, hipStream_t st) {
-  if (first && bx)
-    launch_exp_fwd_r<true, true>(src, dst, hg, tg, scale, bx, rc, st);
-  else if (first)
-    launch_exp_fwd_r<true, false>(src, dst, hg, tg, scale, bx, rc, st);
-  else if (bx)
-    launch_exp_fwd_r<false, true>(src, dst, hg, tg, scale, bx, rc, st);
+// Columns of 16 rows fetch less halo; of 8, there are twice as many and fewer
+// idle rows.  16 where that makes six blocks per CU, adds at most a fifth to the
+// rows, and rows are whole 64-byte pieces (or most of one column).  Seven steps
+// in columns of 8 and 16: 16 x 160 x 192 x 160 (6000 blocks of 16 rows) 3.11 and
+// 2.88 ms, 8 x 96^3 (1728) 318 and 305 us; 2 x 128^3 (1024) 172 and 178, 4 x 80^3
+// (600) 107 and 120; 8 x 128 x 24 x 128 129 and 151; 16 x 182 x 218 x 182 6.02 and
+// 6.42 ms; 8 x 256 x 256 x 24 616 and 566 us.
+template <bool FIRST, bool REC>
+void launch_exp_fwd_c(const float* src, float* dst, const TileGeom& tg, int tz, float scale,
+                      int* bx, int* rc, hipStream_t st) {
+  const HatGeom wide = make_hat(tg, tz, Column<2>::TY), one = make_hat(tg, tz, Column<1>::TY);
+  const bool rows = 5 * Column<2>::TY * wide.nty <= 6 * Column<1>::TY * one.nty;
+  const bool whole = tg.g.d2 % 16 == 0 || (tg.g.d2 > ETX / 2 && tg.g.d2 < ETX);
+  if (wide.total >= 1536 && rows && whole)
+    launch_exp_fwd_r<FIRST, REC, 2>(src, dst, wide, tg, scale, bx, rc, st);
   else
-    launch_exp_fwd_r<false, false>(src, dst, hg, tg, scale, bx, rc, st);
+    launch_exp_fwd_r<FIRST, REC, 1>(src, dst, one, tg, scale, bx, rc, st);
+}
+
+void launch_exp_fwd(const float* src, float* dst, bool first, const TileGeom& tg, int tz,
+                    float scale, int* bx, int* rc, hipStream_t st) {
+  if (first && bx)
+    launch_exp_fwd_c<true, true>(src, dst, tg, tz, scale, bx, rc, st);
+  else if (first)
+    launch_exp_fwd_c<true, false>(src, dst, tg, tz, scale, bx, rc, st);
+  else if (bx)
+    launch_exp_fwd_c<false, true>(src, dst, tg, tz, scale, bx, rc, st);
+  else
+    launch_exp_fwd_c<false, false>(src, dst, tg, tz, scale, bx, rc, st);
 }
 
 // The reach-1 adjoint of one step (check: no records were taken).
@@ -2071,7 +2120,7 @@ void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, co
     return;
   }
   const TileGeom tg = make_tiles(g, n);
-  const HatGeom hg = make_hat(tg, march_tz(tg, n));
+  const int tz = march_tz(tg, n);
   const AuxPtrs ap = aux_ptrs(aux, tg, n, n_sq);
   const bool planes = plane_mode(g, n);
   // the reaches are running maxima: start them at zero (all-zero bits); the
@@ -2118,7 +2167,7 @@ void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, co
         hipLaunchKernelGGL((k_exp_fwd_planes<false, false>), grid, dim3(ENT), 0, st, src, dst,
                            tg, 1.0f, bx, rc);
     } else {
-      launch_exp_fwd(src, dst, t == 0, hg, tg, t == 0 ? scale : 1.0f, bx, rc, st);
+      launch_exp_fwd(src, dst, t == 0, tg, tz, t == 0 ? scale : 1.0f, bx, rc, st);
     }
     prof_end(st, KC_EXP_FWD);
     src = dst;
@@ -2163,7 +2212,7 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, int t, int 
   }
   // each subject is handled by exactly one of the three adjoints (decided on
   // the device from its reach: 1, 2, beyond); the others pass it over
-  const HatGeom hg = make_hat(m.rec, m.tz);
+  const HatGeom hg = make_hat(m.rec, m.tz, HTY);
   const int* later = !recs && t + 1 < n_sq ? rc + ap.reach_stride : nullptr;
   prof_begin(st, KC_EXP_BWD);
   const int n = static_cast<int>(m.rec.total / m.rec.ntiles);
@@ -2236,7 +2285,6 @@ void run_exp_bwd_recompute(const float* v, const float* g_u, float* g_v, float* 
   const TileGeom tg = make_tiles(g, n);
   const BwdGeom bg = make_bwd(tg, n);
   const MarchGeom m = make_march(tg, n, march_tz(tg, n));
-  const HatGeom hg = make_hat(tg, m.tz);
   const AuxPtrs ap = aux_ptrs(aux, tg, n, n_sq);
   const float scale = ldexpf(1.0f, -n_sq);
   launch_fill_f32(reinterpret_cast<float*>(ap.reach),
@@ -2248,7 +2296,7 @@ void run_exp_bwd_recompute(const float* v, const float* g_u, float* g_v, float* 
     for (int k = 0; k < t; ++k) {
       float* dst = ((t - 1 - k) % 2 == 0) ? rec_a : rec_b;
       prof_begin(st, KC_EXP_FWD);
-      launch_exp_fwd(ut, dst, k == 0, hg, tg, k == 0 ? scale : 1.0f, nullptr, nullptr, st);
+      launch_exp_fwd(ut, dst, k == 0, tg, m.tz, k == 0 ? scale : 1.0f, nullptr, nullptr, st);
       prof_end(st, KC_EXP_FWD);
       ut = dst;
     }
