@@ -2096,6 +2096,25 @@ void launch_exp_fwd(const float* src, float* dst, bool first, const TileGeom& tg
     launch_exp_fwd_c<false, false>(src, dst, tg, tz, scale, bx, rc, st);
 }
 
+// One squaring step in the launch's shape.
+void launch_fwd_step(const float* src, float* dst, bool first, bool planes, const TileGeom& tg,
+                     int tz, float scale, int* bx, int* rc, hipStream_t st) {
+  if (!planes) return launch_exp_fwd(src, dst, first, tg, tz, scale, bx, rc, st);
+  const dim3 grid(tg.total * ETZ);
+  if (first && bx)
+    hipLaunchKernelGGL((k_exp_fwd_planes<true, true>), grid, dim3(ENT), 0, st, src, dst, tg, scale,
+                       bx, rc);
+  else if (first)
+    hipLaunchKernelGGL((k_exp_fwd_planes<true, false>), grid, dim3(ENT), 0, st, src, dst, tg, scale,
+                       bx, rc);
+  else if (bx)
+    hipLaunchKernelGGL((k_exp_fwd_planes<false, true>), grid, dim3(ENT), 0, st, src, dst, tg, scale,
+                       bx, rc);
+  else
+    hipLaunchKernelGGL((k_exp_fwd_planes<false, false>), grid, dim3(ENT), 0, st, src, dst, tg,
+                       scale, bx, rc);
+}
+
 // The reach-1 adjoint of one step (check: no records were taken).
 template <bool FIRST, bool CHECK>
 void launch_hat_r(const float* ut, const float* gin, float* gout, const HatGeom& hg, int n,
@@ -2152,23 +2171,7 @@ void run_exp_fwd(const float* v, float* u, float* ckpt, float* tmp, int* aux, co
     int* bx = aux ? ap.boxes + ap.box_stride * t : nullptr;
     int* rc = aux ? ap.reach + ap.reach_stride * t : nullptr;
     prof_begin(st, KC_EXP_FWD);
-    if (planes) {
-      const dim3 grid(tg.total * ETZ);
-      if (t == 0 && aux)
-        hipLaunchKernelGGL((k_exp_fwd_planes<true, true>), grid, dim3(ENT), 0, st, src, dst, tg,
-                           scale, bx, rc);
-      else if (t == 0)
-        hipLaunchKernelGGL((k_exp_fwd_planes<true, false>), grid, dim3(ENT), 0, st, src, dst, tg,
-                           scale, bx, rc);
-      else if (aux)
-        hipLaunchKernelGGL((k_exp_fwd_planes<false, true>), grid, dim3(ENT), 0, st, src, dst, tg,
-                           1.0f, bx, rc);
-      else
-        hipLaunchKernelGGL((k_exp_fwd_planes<false, false>), grid, dim3(ENT), 0, st, src, dst,
-                           tg, 1.0f, bx, rc);
-    } else {
-      launch_exp_fwd(src, dst, t == 0, tg, tz, t == 0 ? scale : 1.0f, bx, rc, st);
-    }
+    launch_fwd_step(src, dst, t == 0, planes, tg, tz, t == 0 ? scale : 1.0f, bx, rc, st);
     prof_end(st, KC_EXP_FWD);
     src = dst;
   }
@@ -2287,6 +2290,7 @@ void run_exp_bwd_recompute(const float* v, const float* g_u, float* g_v, float* 
   const MarchGeom m = make_march(tg, n, march_tz(tg, n));
   const AuxPtrs ap = aux_ptrs(aux, tg, n, n_sq);
   const float scale = ldexpf(1.0f, -n_sq);
+  const bool planes = plane_mode(g, n);
   launch_fill_f32(reinterpret_cast<float*>(ap.reach),
                   static_cast<long long>(ap.reach_stride) * n_sq, 0.0f, st);
   const float* gin = g_u;
@@ -2296,11 +2300,11 @@ void run_exp_bwd_recompute(const float* v, const float* g_u, float* g_v, float* 
     for (int k = 0; k < t; ++k) {
       float* dst = ((t - 1 - k) % 2 == 0) ? rec_a : rec_b;
       prof_begin(st, KC_EXP_FWD);
-      launch_exp_fwd(ut, dst, k == 0, tg, m.tz, k == 0 ? scale : 1.0f, nullptr, nullptr, st);
+      launch_fwd_step(ut, dst, k == 0, planes, tg, m.tz, k == 0 ? scale : 1.0f, nullptr, nullptr,
+                      st);
       prof_end(st, KC_EXP_FWD);
       ut = dst;
     }
-    const bool planes = plane_mode(g, n);
     // u_t stands in place of every step's field
     if (planes) launch_rec(t == 0 ? v : ut, ut, 0, t, 1, tg, scale, ap, false, st);
     float* gout = (t == 0) ? g_v : (((n_sq - 1 - t) % 2 == 0) ? tmp_a : tmp_b);
