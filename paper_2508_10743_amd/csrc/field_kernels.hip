@@ -2,6 +2,8 @@
 // diffusion regulariser, Adam, the centrality activation and the mean atlas.  One thread per voxel, 256-thread
 // blocks, blocks remapped so that each XCD walks a contiguous range of voxels
 // (the gathers of neighbouring voxels then share that XCD's L2).
+#include <type_traits>
+
 #include "darc_kernels.hpp"
 #include "voxel_bodies.hpp"
 
@@ -25,73 +27,95 @@ __device__ __forceinline__ VoxelBlock voxel_block(uint32_t nbx, uint32_t total) 
 
 // -------------------------------------------------------------------- warp
 
-// The warp and its adjoint: a block owns 32 (d2) x 4 (d1) x 2
-// (d0) voxels, so that neighbouring rows' and planes' image corners meet in one
-// CU's cache.  Bound by the gathers: 16 x 160 x 192 x 160 with displacements of
-// 8 voxels, warp and adjoint 1.01 ms; on tiles of 256 consecutive voxels 1.29,
-// 32 x 8 x 1 1.07, 32 x 4 x 4 (512 threads) 1.00, 32 x 8 x 4 (1024) 1.03, two
-// planes per thread 1.16 (0.37 instead of 0.45 ms per warp where the
-// displacements are smooth, but 0.66 instead of 0.59 where they are not).
+// The warp and its adjoint, bound by the gathers of image corners: the more of
+// the neighbouring rows' and planes' corners meet in one CU's cache, the better,
+// so a block owns either a tile of 32 (d2) x 4 (d1) x 2 (d0) voxels or a run of
+// NT consecutive ones.  Against runs of 256 (16 x 160 x 192 x 160 in 442 us at
+// displacements of 1 voxel, 587 of 8; the adjoint into a fresh tensor likewise),
+// times faster at 1 and 8 voxels: tiles 1.0 and 1.28, the adjoint 0.96 and 1.32;
+// runs of 512 1.0 and 1.1, 1024 0.97-1.0 and 1.18, the adjoint 0.96 and 1.19.
 constexpr int kWarpX = 32, kWarpY = 4, kWarpZ = 2;
-constexpr int kWarpNT = kWarpX * kWarpY * kWarpZ;
+constexpr int kWarpTile = kWarpX * kWarpY * kWarpZ;
 
 struct WarpGrid {
   Geom g;
-  int ntx, nty, ntz;
+  FastDiv ntx, nty, ntz;  // tiles per axis; runs: ntx per subject
   uint32_t total;
 };
 
-WarpGrid make_warp_grid(const Geom& g, int n) {
+WarpGrid make_warp_tiles(const Geom& g, int n) {
   WarpGrid w;
   w.g = g;
-  w.ntx = (g.d2 + kWarpX - 1) / kWarpX;
-  w.nty = (g.d1 + kWarpY - 1) / kWarpY;
-  w.ntz = (g.d0 + kWarpZ - 1) / kWarpZ;
-  w.total = static_cast<uint32_t>(w.ntx) * w.nty * w.ntz * n;
+  w.ntx = make_fastdiv((g.d2 + kWarpX - 1) / kWarpX);
+  w.nty = make_fastdiv((g.d1 + kWarpY - 1) / kWarpY);
+  w.ntz = make_fastdiv((g.d0 + kWarpZ - 1) / kWarpZ);
+  w.total = w.ntx.d * w.nty.d * w.ntz.d * n;
+  return w;
+}
+
+WarpGrid make_warp_runs(const Geom& g, int n, int nt) {
+  WarpGrid w;
+  w.g = g;
+  w.ntx = w.nty = w.ntz = make_fastdiv(blocks_for(g.V, nt));
+  w.total = w.ntx.d * n;
   return w;
 }
 
 struct WarpVoxel {
   uint32_t s;
   int x0, x1, x2;
-  bool in;  // inside the volume
+  uint32_t lin;  // 0 outside the volume
+  bool in;       // inside the volume
 };
 
+// NT: length of a run, or 0 for tiles.
+template <int NT>
 __device__ __forceinline__ WarpVoxel warp_voxel(const WarpGrid& w) {
-  uint32_t b = xcd_remap(blockIdx.x, w.total);
+  const uint32_t b = xcd_remap(blockIdx.x, w.total);
   WarpVoxel v;
-  v.x2 = static_cast<int>(b % w.ntx) * kWarpX + static_cast<int>(threadIdx.x) % kWarpX;
-  b /= w.ntx;
-  v.x1 = static_cast<int>(b % w.nty) * kWarpY + static_cast<int>(threadIdx.x) / kWarpX % kWarpY;
-  b /= w.nty;
-  v.x0 = static_cast<int>(b % w.ntz) * kWarpZ + static_cast<int>(threadIdx.x) / (kWarpX * kWarpY);
-  v.s = b / w.ntz;
-  v.in = v.x0 < w.g.d0 && v.x1 < w.g.d1 && v.x2 < w.g.d2;
+  const uint32_t by = fdiv(b, w.ntx), bx = b - by * w.ntx.d;
+  if (NT == 0) {
+    const uint32_t bz = fdiv(by, w.nty), ty = by - bz * w.nty.d;
+    v.s = fdiv(bz, w.ntz);
+    const uint32_t tz = bz - v.s * w.ntz.d;
+    v.x2 = static_cast<int>(bx * kWarpX + threadIdx.x % kWarpX);
+    v.x1 = static_cast<int>(ty * kWarpY + threadIdx.x / kWarpX % kWarpY);
+    v.x0 = static_cast<int>(tz * kWarpZ + threadIdx.x / (kWarpX * kWarpY));
+    v.in = v.x0 < w.g.d0 && v.x1 < w.g.d1 && v.x2 < w.g.d2;
+    v.lin = v.in ? static_cast<uint32_t>((v.x0 * w.g.d1 + v.x1) * w.g.d2 + v.x2) : 0u;
+  } else {
+    const uint32_t lin = bx * NT + threadIdx.x;
+    v.s = by;
+    v.in = lin < static_cast<uint32_t>(w.g.V);
+    v.lin = v.in ? lin : 0u;
+    voxel_coords(w.g, static_cast<int>(v.lin), v.x0, v.x1, v.x2);
+  }
   return v;
 }
 
-__global__ __launch_bounds__(kWarpNT) void k_warp(const float* __restrict__ img,
-                                                 const float* __restrict__ u,
-                                                 float* __restrict__ out, WarpGrid w) {
+template <int NT>
+__global__ __launch_bounds__(NT ? NT : kWarpTile) void k_warp(const float* __restrict__ img,
+                                                              const float* __restrict__ u,
+                                                              float* __restrict__ out, WarpGrid w) {
   const Geom& g = w.g;
-  const WarpVoxel v = warp_voxel(w);
+  const WarpVoxel v = warp_voxel<NT>(w);
   const float* I = img + static_cast<size_t>(v.s) * g.V;
   const float* f = u + static_cast<size_t>(v.s) * 3 * g.V;
   const MaskedOut o = masked_out(out + static_cast<size_t>(v.s) * g.V, static_cast<uint32_t>(g.V));
-  const uint32_t lin = v.in ? static_cast<uint32_t>((v.x0 * g.d1 + v.x1) * g.d2 + v.x2) : 0u;
-  const float w0 = ld_at(f, lin), w1 = ld_at(f + g.V, lin),
-              w2 = ld_at(f + 2 * static_cast<size_t>(g.V), lin);
-  store_masked(o, lin, sample_zero_value(I, g, v.x0, v.x1, v.x2, w0, w1, w2), v.in);
+  const float w0 = ld_at(f, v.lin), w1 = ld_at(f + g.V, v.lin),
+              w2 = ld_at(f + 2 * static_cast<size_t>(g.V), v.lin);
+  store_masked(o, v.lin, sample_zero_value(I, g, v.x0, v.x1, v.x2, w0, w1, w2), v.in);
 }
 
 // ACC: added to gu, otherwise gu is overwritten.
-template <bool ACC, bool STREAM>
-__global__ __launch_bounds__(kWarpNT) void k_warp_bwd(const float* __restrict__ img,
-                                                     const float* __restrict__ u,
-                                                     const float* __restrict__ gout,
-                                                     float* __restrict__ gu, WarpGrid w) {
+template <bool ACC, bool STREAM, int NT>
+__global__ __launch_bounds__(NT ? NT : kWarpTile) void k_warp_bwd(const float* __restrict__ img,
+                                                                  const float* __restrict__ u,
+                                                                  const float* __restrict__ gout,
+                                                                  float* __restrict__ gu,
+                                                                  WarpGrid w) {
   const Geom& g = w.g;
-  const WarpVoxel v = warp_voxel(w);
+  const WarpVoxel v = warp_voxel<NT>(w);
   const float* I = img + static_cast<size_t>(v.s) * g.V;
   const float* go = gout + static_cast<size_t>(v.s) * g.V;
   const size_t off = static_cast<size_t>(v.s) * 3 * g.V;
@@ -100,7 +124,7 @@ __global__ __launch_bounds__(kWarpNT) void k_warp_bwd(const float* __restrict__ 
 #pragma unroll
   for (int c = 0; c < 3; ++c)
     o[c] = masked_out(gu + off + static_cast<size_t>(c) * g.V, static_cast<uint32_t>(g.V));
-  const uint32_t lin = v.in ? static_cast<uint32_t>((v.x0 * g.d1 + v.x1) * g.d2 + v.x2) : 0u;
+  const uint32_t lin = v.lin;
   float uv[3], old[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -341,31 +365,74 @@ RegW make_regw(const Geom& g, int ncomp, float lam) {
   return r;
 }
 
+namespace {
+
+// Tiles where rows are whole tiles and the other axes add at most a twentieth
+// (32 x 4 x 2 on d2 = 97: 0.8 of the speed of runs of 256; 16 x 182 x 218 x 182,
+// off the line grid besides: 0.96 and 1.25, runs of 1024 1.00 and 1.21); not where
+// an accumulated adjoint walks planes of a multiple of 16 KB (128 x 128: 0.98 and
+// 0.94, runs of 1024 1.05 and 1.11).  Runs of 1024 where image and displacements
+// are larger than the last-level cache, else of 512 (8 x 91 x 109 x 91: 1.05 and
+// 1.03, of 1024 1.00 and 1.03), and of 256 where there are few, or where more
+// would exceed the threads of a launch.
+int warp_run(const Geom& g, int n, bool acc) {
+  const long long nv = static_cast<long long>(n) * g.V;
+  const long long tiles = static_cast<long long>((g.d2 + kWarpX - 1) / kWarpX) *
+                          ((g.d1 + kWarpY - 1) / kWarpY) * ((g.d0 + kWarpZ - 1) / kWarpZ) * n;
+  if (g.d2 % kWarpX == 0 && 20 * tiles * kWarpTile <= 21 * nv &&
+      tiles * kWarpTile < (1ll << 32) && !(acc && g.plane % 4096 == 0))
+    return 0;
+  const int nt = nv * 16 > static_cast<long long>(kStreamBytes) ? 1024 : nv >= (1 << 18) ? 512 : 256;
+  return static_cast<long long>(blocks_for(g.V, nt)) * nt * n < (1ll << 32) ? nt : 256;
+}
+
+// Calls f(the kernel's NT as a constant, its grid, its threads per block).
+template <class F>
+void with_warp_grid(const Geom& g, int n, bool acc, F f) {
+  const int nt = warp_run(g, n, acc);
+  if (nt == 0)
+    f(std::integral_constant<int, 0>{}, make_warp_tiles(g, n), kWarpTile);
+  else if (nt == 256)
+    f(std::integral_constant<int, 256>{}, make_warp_runs(g, n, nt), nt);
+  else if (nt == 512)
+    f(std::integral_constant<int, 512>{}, make_warp_runs(g, n, nt), nt);
+  else
+    f(std::integral_constant<int, 1024>{}, make_warp_runs(g, n, nt), nt);
+}
+
+template <bool ACC, bool STREAM>
+void warp_bwd_grid(const float* img, const float* u, const float* gout, float* gu, const Geom& g,
+                   int n, hipStream_t st) {
+  with_warp_grid(g, n, ACC, [&](auto nt, const WarpGrid& w, int threads) {
+    hipLaunchKernelGGL((k_warp_bwd<ACC, STREAM, decltype(nt)::value>), dim3(w.total), dim3(threads),
+                       0, st, img, u, gout, gu, w);
+  });
+}
+
+}  // namespace
+
 void launch_warp(const float* img, const float* u, float* out, const Geom& g, int n,
                  hipStream_t st) {
-  const WarpGrid w = make_warp_grid(g, n);
   prof_begin(st, KC_WARP);
-  hipLaunchKernelGGL(k_warp, dim3(w.total), dim3(kWarpNT), 0, st, img, u, out, w);
+  with_warp_grid(g, n, false, [&](auto nt, const WarpGrid& w, int threads) {
+    hipLaunchKernelGGL(k_warp<decltype(nt)::value>, dim3(w.total), dim3(threads), 0, st, img, u, out,
+                       w);
+  });
   prof_end(st, KC_WARP);
 }
 
 void launch_warp_bwd(const float* img, const float* u, const float* gout, float* gu, bool acc,
                      const Geom& g, int n, hipStream_t st) {
-  const WarpGrid w = make_warp_grid(g, n);
   const bool stream = streamed(gu, static_cast<size_t>(n) * 3 * g.V, g);
   prof_begin(st, KC_WARP_BWD);
   if (acc && stream)
-    hipLaunchKernelGGL((k_warp_bwd<true, true>), dim3(w.total), dim3(kWarpNT), 0, st, img, u, gout,
-                       gu, w);
+    warp_bwd_grid<true, true>(img, u, gout, gu, g, n, st);
   else if (acc)
-    hipLaunchKernelGGL((k_warp_bwd<true, false>), dim3(w.total), dim3(kWarpNT), 0, st, img, u, gout,
-                       gu, w);
+    warp_bwd_grid<true, false>(img, u, gout, gu, g, n, st);
   else if (stream)
-    hipLaunchKernelGGL((k_warp_bwd<false, true>), dim3(w.total), dim3(kWarpNT), 0, st, img, u, gout,
-                       gu, w);
+    warp_bwd_grid<false, true>(img, u, gout, gu, g, n, st);
   else
-    hipLaunchKernelGGL((k_warp_bwd<false, false>), dim3(w.total), dim3(kWarpNT), 0, st, img, u, gout,
-                       gu, w);
+    warp_bwd_grid<false, false>(img, u, gout, gu, g, n, st);
   prof_end(st, KC_WARP_BWD);
 }
 
