@@ -1622,11 +1622,13 @@ void launch_conv3d(const uint16_t* x0, const uint16_t* x1, const uint16_t* w, co
       // Bricks of 8 rows where they compute no more rows than those of 4 (64 ->
       // 32 at 4 x 48 x 56 x 48: 80 us, of 4 92; 192 -> 64 with 28 rows: 73, of
       // 4 65), except for FP32 outputs, whose stores want the blocks in flight
-      // (that adjoint: 400 us, of 4 353)
+      // (that adjoint: 400 us, of 4 353), where there is one for each CU (96 -> 32
+      // at 2 x 30 x 16 x 30: 64 bricks of 8 rows 24 us, 128 of 4 17), and where
+      // the channels leave by vector stores (16 -> 3 at 64^3: 13.8 us, of 4 11.2)
       const uint32_t gy = static_cast<uint32_t>(cg.cout <= 16 ? 1 : (cg.cout + 31) / 32);
-      if (y16 && (cg.o1 + 7) / 8 * 8 <= nby * kLdsMT) {
-        const int nby8 = (cg.o1 + 7) / 8;
-        const uint32_t gx8 = gx / nby * nby8;
+      const int nby8 = (cg.o1 + 7) / 8;
+      const uint32_t gx8 = gx / nby * nby8;
+      if (y16 && cg.cout % 8 == 0 && nby8 * 8 <= nby * kLdsMT && gx8 * gy >= 256) {
         if (cg.cout <= 16)
           conv3d_rows<1, 8>(mode, dim3(gx8, gy), x0, x1, w, bias, y16, y32, cg, nbz, nby8, nbx, st);
         else
