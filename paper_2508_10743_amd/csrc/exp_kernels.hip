@@ -125,8 +125,8 @@ __device__ __forceinline__ void flush_reach(int rmax, int* reach, int s) {
 }
 
 // Further entries of reach[s * 8 ..], zeroed with the reaches and set by the
-// reach-1 adjoint: it met a gradient that is not finite; or (CHECK: no records
-// were taken) a cell beyond reach 1, or it did not try.
+// reach-1 adjoint: it met a gradient that is not finite, or too large for it; or
+// (CHECK: no records were taken) a cell beyond reach 1, or it did not try.
 constexpr int kNonFinite = 6, kFar = 7;
 
 __device__ __forceinline__ int max_reach(const int* rc) {
@@ -785,9 +785,12 @@ __device__ __forceinline__ void exp_bwd_tile(TiledBwdLds& L, int s, int tile,
 // g = 0.
 //
 // A source contributes to the eight corners of its cell only, so a target
-// next to it must not see 0 * g when g is not finite.  A block that meets
-// such a g says so in its subject's record (kNonFinite), and the reach-2
-// kernel, launched after this one, then computes that subject again.
+// next to it must not see 0 * g when g is not finite; and the doubled sums of up
+// to 27 sources must not leave the range of FP32 where the gradient does not.  A
+// block that meets a g that is not finite or beyond kHatMax says so in its
+// subject's record (kNonFinite), and the reach-2 kernel, launched after this
+// one, then computes that subject again.
+constexpr float kHatMax = 0x1p120f;
 struct HatLds {
   float uring[3 * HSLOT];  // u_t of planes q-2, q-1, q (slot p % 3)
   float4 src4[HHP];        // plane q: clamped u (scaled in the first step), g0
@@ -945,7 +948,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
         pg[j][c] = load_masked(fg[c], zo + poff[j]);
       }
   };
-  bool bad = false;  // a g that is not finite was staged
+  bool bad = false;  // a g that is not finite, or too large, was staged
   auto stage = [&](int z) {
     const int sl = (z + 3) % 3;
     const uint32_t rz = hat_range(z, g.d0);
@@ -973,7 +976,7 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
                             u[2] >= -1.0f && u[2] < 1.0f)) {
         L.stop = 1;
       }
-      bad |= !__builtin_isfinite(pg[j][0] + pg[j][1] + pg[j][2]);
+      bad |= !(fabsf(pg[j][0]) + fabsf(pg[j][1]) + fabsf(pg[j][2]) < kHatMax);
       L.src4[e] = make_float4(u[0], u[1], u[2], pg[j][0]);
       L.src2[e] = make_float2(pg[j][1], pg[j][2]);
     }

@@ -106,3 +106,19 @@ def test_outward_faces_stay_with_the_reach_1_kernel():
         assert np.isfinite(clean[i]).all() and not np.isfinite(other[i]).all()
         inner = np.s_[:, 4:8, 4:-4, 4:-4]  # one source in each cell
         assert np.array_equal(clean[i][inner], other[i][inner]) == (i == 1)
+
+
+@pytest.mark.parametrize("size", [1.5e38, 1e37])
+def test_gradient_near_the_end_of_the_range(size):
+    """A gradient whose doubled partial sums would leave FP32 gives the finite
+    values that it has."""
+    dims = (19, 20, 40)
+    u, gr = step(dims, [-0.3])
+    u[0, :, 8:14, 5:12, 14:30] = 0.0  # where g + J^T g + S^T g is g at its voxel twice
+    gr *= 1e-3 * size
+    gr[0, 1, 11, 8, 20] = size
+    ref = O.squaring_step_bwd(u[0], gr[0]) * 0.5
+    got = D.exp_svf_bwd(torch.from_numpy(u * 2.0).cuda(), None, torch.from_numpy(gr).cuda(),
+                        1).cpu().numpy()
+    assert np.isfinite(got).all()
+    assert np.linalg.norm(got[0].astype(np.float64) - ref) <= TOL * np.linalg.norm(ref)
