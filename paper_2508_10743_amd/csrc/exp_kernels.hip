@@ -850,11 +850,11 @@ __device__ __forceinline__ float hat_clamp(float u, uint32_t range) {
   return __builtin_amdgcn_fmed3f(u, -static_cast<float>(range & 255u),
                                  static_cast<float>((range >> 8) & 255u));
 }
-// Whether the cell of a clamped displacement lies beyond reach 1.  (One voxel
-// before the far face a clamped +1 lies in the last cell, at fraction 1; a NaN
-// is clamped to the low end, as everywhere.)
+// Whether the cell of a displacement, clamped near the faces, lies beyond reach
+// 1.  (One voxel before the far face a clamped +1 lies in the last cell, at
+// fraction 1; a NaN points to the low face, as everywhere.)
 __device__ __forceinline__ bool hat_beyond(float w, uint32_t range) {
-  return w < -1.0f || (w >= 1.0f && ((range >> 8) & 255u) == 2u);
+  return !(w >= -1.0f) || (w >= 1.0f && ((range >> 8) & 255u) == 2u);
 }
 
 // CHECK: the forward took no records.  The kernel then looks at the
@@ -969,12 +969,11 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
         u[0] = hat_clamp(u[0], rz);
         u[1] = hat_clamp(u[1], prange[j] >> 16);
         u[2] = hat_clamp(u[2], prange[j]);
-        if (CHECK && (hat_beyond(u[0], rz) || hat_beyond(u[1], prange[j] >> 16) ||
-                      hat_beyond(u[2], prange[j])))
+      }
+      // (the ring's voxels are other columns' own)
+      if (CHECK && j < 2 && !(fabsf(u[0]) < 1.0f && fabsf(u[1]) < 1.0f && fabsf(u[2]) < 1.0f)) {
+        if (hat_beyond(u[0], rz) || hat_beyond(u[1], prange[j] >> 16) || hat_beyond(u[2], prange[j]))
           L.stop = 1;
-      } else if (CHECK && !(u[0] >= -1.0f && u[0] < 1.0f && u[1] >= -1.0f && u[1] < 1.0f &&
-                            u[2] >= -1.0f && u[2] < 1.0f)) {
-        L.stop = 1;
       }
       bad |= !(fabsf(pg[j][0]) + fabsf(pg[j][1]) + fabsf(pg[j][2]) < kHatMax);
       L.src4[e] = make_float4(u[0], u[1], u[2], pg[j][0]);
