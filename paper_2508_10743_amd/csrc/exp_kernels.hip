@@ -4,17 +4,18 @@
 // clamping; the first step reads v and scales it by 2^-N on the fly.
 //
 // Adjoint step: g_t(y) = g(y) + J_t(y)^T g(y) + sum_x sum_k [corner_k(x) = y] w_k(x) g(x)
-// with g = g_{t+1}.  The scatter term is computed owner-side, as a gather: a
-// block owns one output tile, bins the source voxels whose trilinear cells
-// touch it by cell (one LDS integer atomic per source), and then every output
-// voxel sums over the sources binned in its 8 neighbouring cells.  Which
-// source voxels to look at follows from the offsets (cell index - voxel
-// index) the forward step recorded per tile, so no global atomics and no
-// zero-fill pass are needed, and each output value is written once.  (Float
-// atomics in LDS are serialised lane by lane on this hardware: scattering the
-// 24 weighted corner values of every source with them costs an order of
-// magnitude more than this binning.)  Forward tiles are 32 (d2) x 8 (d1) x 8
-// (d0) voxels, adjoint tiles 32 x 4 x 4.
+// with g = g_{t+1}.  The scatter term is computed owner-side, as a gather, so
+// that no global atomics and no zero-fill pass are needed and each output value
+// is written once: where every cell lies within one voxel, a target sums its 27
+// neighbours, weighted by hat functions of their displacements; beyond, a block
+// bins the source voxels whose trilinear cells touch its targets by cell (one LDS
+// integer atomic per source) and every target sums over the sources binned in
+// its 8 neighbouring cells.  Which source voxels to look at follows from the
+// offsets (cell index - voxel index) recorded per tile of 32 (d2) x 8 (d1) x 8
+// (d0) voxels by the forward step, or before the adjoint for the subjects that
+// need them.  (Float atomics in LDS are serialised lane by lane on this hardware:
+// scattering the 24 weighted corner values of every source with them costs an
+// order of magnitude more than the binning.)
 #include <climits>
 
 #include "darc_kernels.hpp"
@@ -71,7 +72,9 @@ __device__ __forceinline__ int wave_max(int x) { return wave_extreme<true>(x); }
 // touches lie in x + [min, max + 1].  reach[s * 8 + d] = max(0, -min over tiles
 // of the min offset) and reach[s * 8 + 3 + d] = max(0, max over tiles of the
 // max offset + 1): how far below / above itself any voxel of the subject can
-// scatter (zeroed before).  Tiles are 32 (d2) x 8 (d1) x 8 (d0).
+// scatter (zeroed before).  Tiles are 32 (d2) x 8 (d1) x 8 (d0).  The squaring
+// steps start each box at offsets [-1, 0] and raise a reach from 2 on only: what
+// lies within needs no record.
 __device__ __forceinline__ void write_record(int mn0, int mn1, int mn2, int mx0, int mx1, int mx2,
                                              int (*red)[ENT / 64], int* __restrict__ boxes,
                                              int s, int tile, int ntiles, int& rmax) {
@@ -187,13 +190,15 @@ __global__ __launch_bounds__(ENT) void k_exp_rec(const float* __restrict__ v,
 }
 
 // ---------------------------------------------------------------------------
-// Marching kernels: a block owns a 32 x 8 column of the (d1, d2) plane and
-// walks a chunk of planes along d0.  A ring of the last planes of u (and g)
-// with a one-voxel halo in d1 and d2 lives in LDS; the next plane is loaded
-// into registers while the current one is computed, so every value is read
-// from memory once and loads overlap compute.
+// Marching kernels: a block owns a column of the (d1, d2) plane, 32 wide, and
+// walks a chunk of planes along d0.  A ring of the last planes of u with a halo
+// in d1 and d2 lives in LDS; the next plane (of the adjoints also of g) is loaded
+// into registers while the current one is computed, so every value is read from
+// memory once and loads overlap compute.  Columns of 8 or 16 rows with a
+// one-voxel halo for the squaring step (Column below), of 16 for its reach-1
+// adjoint, of 8 with a two-voxel halo for the reach-2 adjoint (MarchGeom).
 struct MarchGeom {
-  TileGeom rec;  // record tiling (same 32 x 8 columns, 8 planes per record)
+  TileGeom rec;  // record tiling (the same 32 x 8 columns, 8 planes per record)
   int nzc, tz;   // chunks along d0 and their length (a multiple of ETZ)
   uint32_t total;
 };
@@ -584,10 +589,10 @@ __device__ __forceinline__ void exp_bwd_tile(TiledBwdLds& L, int s, int tile,
   // 2. bin the source voxels whose cell base lies in [O - 1, L].  A source x
   //    of forward tile s has its cell base in x + [min, max] (the recorded
   //    offsets), so only x_d in [O_d - 1 - max_d, L_d - min_d] can qualify;
-  //    candidate forward tiles come from the subject-wide reach (recorded
-  //    only from 2 on by the plane-parallel forward).  The union
-  //    box of those sub-boxes is swept as one flattened range, four sources
-  //    per thread at a time with all their loads issued before any is used.
+  //    candidate forward tiles come from the subject-wide reach (1 where none
+  //    is recorded).  The union box of those sub-boxes is swept as one
+  //    flattened range, four sources per thread at a time with all their loads
+  //    issued before any is used.
   int rc[6];
 #pragma unroll
   for (int k = 0; k < 6; ++k) rc[k] = max(reach[s * 8 + k], 1);
@@ -972,7 +977,8 @@ __global__ __launch_bounds__(ENT, 4) void k_exp_bwd_hat(const float* __restrict_
       }
       // (the ring's voxels are other columns' own)
       if (CHECK && j < 2 && !(fabsf(u[0]) < 1.0f && fabsf(u[1]) < 1.0f && fabsf(u[2]) < 1.0f)) {
-        if (hat_beyond(u[0], rz) || hat_beyond(u[1], prange[j] >> 16) || hat_beyond(u[2], prange[j]))
+        if (hat_beyond(u[0], rz) || hat_beyond(u[1], prange[j] >> 16) ||
+            hat_beyond(u[2], prange[j]))
           L.stop = 1;
       }
       bad |= !(fabsf(pg[j][0]) + fabsf(pg[j][1]) + fabsf(pg[j][2]) < kHatMax);
@@ -1268,9 +1274,9 @@ __global__ __launch_bounds__(ENT) void k_exp_bwd_small(const float* __restrict__
 }
 
 // Adjoint of one squaring step, marching, for a subject whose cell offsets
-// lie in [-2, 1] on every axis and reach beyond [-1, 0] somewhere (reach 2:
-// roughly 1 <= max |u_t| < 2, the later squaring steps of moderate
-// deformations).  Sources are binned by cell, one cell plane live at a time: a
+// lie in [-2, 1] on every axis (reach 2: roughly 1 <= max |u_t| < 2, the later
+// squaring steps of moderate deformations; and the subjects within [-1, 0] that
+// the reach-1 kernel leaves).  Sources are binned by cell, one cell plane live at a time: a
 // source of plane p falls in cell planes p-2 .. p+1, so cell plane z is filled from
 // the sources of planes z-1 .. z+2, whose cells are computed once, when their
 // plane is staged, and kept in registers for four iterations; sources up to
@@ -1470,7 +1476,7 @@ __device__ __forceinline__ void exp_bwd_march2(March2Lds& L, const MarchGeom& m,
       }
     }
   };
-  // one pass over the live cell plane (as in the reach-1 kernel)
+  // one pass over the live cell plane serves the targets of planes z and z + 1
   auto gather = [&](float (&lo)[3], float (&up)[3], bool upper) {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
@@ -1761,8 +1767,9 @@ AuxPtrs aux_ptrs(int* aux, const TileGeom& tg, int n, int n_sq) {
 // memory.  With REC the block merges cell offsets beyond [-1, 0] into the
 // tile's record (which starts at that range) and the subject's reaches, which
 // count from 2 on: the atomics of every plane into its tile's record took as
-// long as the step itself (6.1 against 3.8 us at 4 x 32^3).  Blocks are (subject, tile, plane), so a small volume
-// gets eight times the blocks of the marching kernel and no serial planes.
+// long as the step itself (6.1 against 3.8 us at 4 x 32^3).  Blocks are
+// (subject, tile, plane), so a small volume gets eight times the blocks of the
+// marching kernel and no serial planes.
 template <bool FIRST, bool REC>
 __device__ __forceinline__ void exp_fwd_plane_body(int (*red)[ENT / 64], uint32_t blk,
                                                    const float* __restrict__ src,
@@ -1941,7 +1948,7 @@ __global__ __launch_bounds__(ENT) void k_iter_fused(IterArgs a) {
   const size_t fs = static_cast<size_t>(a.tg.total / a.tg.ntiles) * 3 * g.V;
   unsigned nbar = 0;
   // the records are running minima / maxima: start the reaches at zero and
-  // the boxes empty
+  // the boxes at offsets [-1, 0]
   {
     const long long cnt = static_cast<long long>(a.reach_stride) * a.n_sq;
     for (long long i = static_cast<long long>(blockIdx.x) * ENT + threadIdx.x; i < cnt;
@@ -2024,15 +2031,17 @@ size_t exp_aux_bytes(const Geom& g, int n, int n_sq) {
          sizeof(int);
 }
 
-// Chunk length along d0 of the marching kernels: long chunks amortise the two
-// planes of ramp-up; shorter ones give small cohorts enough blocks.
+// Chunk length along d0 of the marching kernels.
 int march_tz(const TileGeom& tg, int n) {
   const int tuned = tuned_tz(TUNE_EXP, tg.g, n);
   if (tuned > 1) return tuned;
   if (tuned < 0) return ETZ;  // plane-parallel kernels; the chunk is not used
   // long chunks amortise the ramp-up planes, short ones keep each block's
   // planes in flight within L2 (64 planes measured no faster than 32 and
-  // fetched more from HBM); shorter still for small cohorts
+  // fetched more from HBM); shorter still until there are 4096 columns of 8 rows
+  // (2048 of 16): seven adjoint steps of 4 x 160 x 192 x 160 in chunks of 8, 16 and
+  // 32 planes 1.60, 1.57 and 1.77 ms (taken: 16), 8 x 96^3 641, 635 and 806 us
+  // (8), 4 x 128^3 718, 679 and 819 (8), 4 x 96 x 112 x 96 383, 450 and 644 (8)
   int tz = 32;
   while (tz > ETZ && static_cast<long long>(tg.ntx) * tg.nty * ((tg.g.d0 + tz - 1) / tz) * n < 4096)
     tz /= 2;
@@ -2043,8 +2052,10 @@ int march_tz(const TileGeom& tg, int n) {
 // tile per block (k_exp_fwd_planes) and an adjoint tile per block
 // (k_exp_bwd_small), no marching.  It wins on small volumes, where the marching kernels' serial
 // planes are the whole cost (4 x 32^3: half the time per sweep).
-// Untuned, it is taken when the marching grid would hold fewer than four
-// blocks per CU even with 8-plane chunks.
+// Untuned, it is taken where 8-plane chunks make fewer than 1024 columns of 8
+// rows (about 512 of the adjoint's 16), where the adjoint is even: seven steps and
+// seven adjoints of 4 x 64^3 (512) 83 and 164 us, marching 73 and 220; 4 x 72^3
+// (972) 122 and 269, 94 and 275; 4 x 80^3 (1200) 144 and 310, 107 and 292.
 bool plane_mode(const Geom& g, int n) {
   const int tuned = tuned_tz(TUNE_EXP, g, n);
   if (tuned != 0) return tuned < 0;
@@ -2215,8 +2226,9 @@ void launch_bwd_step(const float* ut, const float* gin, float* gout, int t, int 
     prof_end(st, KC_EXP_BWD);
     return;
   }
-  // each subject is handled by exactly one of the three adjoints (decided on
-  // the device from its reach: 1, 2, beyond); the others pass it over
+  // each subject's result comes from one of the three adjoints, decided on the
+  // device from its reach (1, 2, beyond) and the reach-1 kernel's marks; what
+  // the reach-1 kernel wrote of a subject that it left is overwritten
   const HatGeom hg = make_hat(m.rec, m.tz, HTY);
   const int* later = !recs && t + 1 < n_sq ? rc + ap.reach_stride : nullptr;
   prof_begin(st, KC_EXP_BWD);

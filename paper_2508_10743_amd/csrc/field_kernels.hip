@@ -1,7 +1,8 @@
 // Voxel-parallel kernels of libdarc: warping and its adjoint, MSE, the
-// diffusion regulariser, Adam, the centrality activation and the mean atlas.  One thread per voxel, 256-thread
-// blocks, blocks remapped so that each XCD walks a contiguous range of voxels
-// (the gathers of neighbouring voxels then share that XCD's L2).
+// diffusion regulariser, Adam, the centrality activation and the mean atlas.
+// One thread per voxel, blocks of 256 threads (the warp: up to 1024) remapped so
+// that each XCD walks a contiguous range of voxels (the gathers of neighbouring
+// voxels then share that XCD's L2).
 #include <type_traits>
 
 #include "darc_kernels.hpp"

@@ -1436,7 +1436,7 @@ void launch_conv_wgrad(const uint16_t* dz, int cz, const uint16_t* x0, const uin
     // remain, so that the 3072 resident at once hold the launch (longer runs
     // mean fewer atomics on the same gradient entries: the output layer, 2
     // groups, 445 us in 4032 waves and 337 in 2016; 96 -> 32 at 4 x 48 x 56 x
-    // 48 312 us in 3024, 334 in 2016)
+    // 48 216 us in 6048, 174 in 3024, 203 in 1512)
     // Rows per K step: 4 (8 voxels each) where d2 is a multiple of 8, so
     // that no lane of a step falls past the row, else one row of 32
     const int rr = cg.o2 % 8 == 0 ? 4 : 1;
