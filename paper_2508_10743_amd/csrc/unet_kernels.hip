@@ -1443,11 +1443,12 @@ void launch_conv_wgrad(const uint16_t* dz, int cz, const uint16_t* x0, const uin
     const uint32_t ngrp = static_cast<uint32_t>((cg.c0 + cg.c1) / 8);
     // channel groups per block: 4 or 2 where they divide each tensor's
     // channels, so that a block stages 64 or 32 contiguous bytes per position;
-    // 4 from eight groups on (64 -> 64 at 4 x 40^3 244 us in blocks of 4, 261 of 2;
-    // 32 -> 16 at 4 x 24^3 78 us and 62: 216 blocks of 4, less than one per CU)
-    const uint32_t gb = ngrp >= 8 && cg.c0 % 32 == 0 && cg.c1 % 32 == 0 ? 4
-                        : cg.c0 % 16 == 0 && cg.c1 % 16 == 0            ? 2
-                                                                        : 1;
+    // 4 unless that makes one block of a whole run of steps (weights alone, blocks
+    // of 4 and 2: 32 -> 16 at 4 x 24^3 60 and 45 us, at 96 x 112 x 96 131 and 120;
+    // 32 -> 32 there 153 and 154, 32 -> 96 284 and 314, 64 -> 64 419 and 567)
+    const uint32_t gb = ngrp * gz >= 8 && cg.c0 % 32 == 0 && cg.c1 % 32 == 0 ? 4
+                        : cg.c0 % 16 == 0 && cg.c1 % 16 == 0                 ? 2
+                                                                             : 1;
     const int wv = 32 / rr;
     const long long nsteps = cg.nvox / (static_cast<long long>(cg.o1) * cg.o2) *
                              ((cg.o1 + rr - 1) / rr) * ((cg.o2 + wv - 1) / wv);
